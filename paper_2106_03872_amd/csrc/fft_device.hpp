@@ -220,6 +220,31 @@ template <> struct alt_plan<96> { using list = radix_list<8, 12>; };
 template <int N, int V> struct plan_v { using list = typename plan<N>::list; };
 template <int N> struct plan_v<N, 1> { using list = typename alt_plan<N>::list; };
 
+// LDS layout of the twiddles.  A two-stage plan R1 * R2 uses them in its last
+// stage only, W^{q k} for output element q < R2 of butterfly k < R1: they are
+// staged as rows [k][q] (R1 * R2 = N entries), so a butterfly's twiddles are
+// consecutive words behind one address.  (Indexing W by q k cost a multiply
+// and an add per twiddle: 18 of them per transform pair of the x-pass.)  Other
+// plans keep W^j at index j.
+template <class L> struct plan_info;
+template <int... Rs> struct plan_info<radix_list<Rs...>> {
+  static constexpr int stages = sizeof...(Rs);
+  static constexpr int last = (Rs, ...);
+};
+template <int N, int V = 0>
+constexpr bool twiddle_rows = plan_info<typename plan_v<N, V>::list>::stages == 2;
+// table position i of the staged twiddles -> power of W
+template <int N, int V = 0>
+__device__ __forceinline__ int twiddle_power(int i) {
+  constexpr int R = plan_info<typename plan_v<N, V>::list>::last;
+  return twiddle_rows<N, V> ? (i % R) * (i / R) : i;
+}
+// stage the twiddles of length N (global: W^j at j) into LDS, block-collective
+template <int N, int NT, int V = 0, typename T>
+__device__ __forceinline__ void stage_twiddles(T* lds, const T* __restrict__ g) {
+  for (int i = threadIdx.x; i < N; i += NT) lds[i] = g[twiddle_power<N, V>(i)];
+}
+
 // Where a stage reads from / writes to.  LDS stages work in place on the
 // batch buffer; the first stage may instead pull its inputs from a loader
 // functor and the last stage may push its outputs to a store functor.
@@ -244,6 +269,35 @@ __device__ __forceinline__ void st_stream(T* p, T x) {
   using V = typename native2<T>::type;
   const V v = {x.x, x.y};
   __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+}
+
+// Buffer access: a 128-bit resource of one array (uniform base, size in
+// bytes) and a 32-bit byte offset per lane.  The hardware checks the offset
+// against the size: loads beyond it return zero and stores beyond it are
+// dropped, so the zeros outside the sphere's planes and the ragged last tile
+// need no branch, no zero fill and no 64-bit address per element, only an
+// offset set to OOB.  Accesses stream past L2 (non-temporal) or not by NT.
+typedef __amdgpu_buffer_rsrc_t gbuf;
+constexpr unsigned OOB = 0x7ffffff0u;   // beyond every buffer (arrays here are below 2^30 bytes)
+__device__ __forceinline__ gbuf make_gbuf(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+template <typename T, bool NT = false>
+__device__ __forceinline__ T buf_load(gbuf r, unsigned off) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "1, 2 or 4 words");
+  constexpr int aux = NT ? 2 : 0;
+  if constexpr (sizeof(T) == 16) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, aux));
+  else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, aux));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, aux));
+}
+template <bool NT = false, typename T>
+__device__ __forceinline__ void buf_store(gbuf r, unsigned off, T x) {
+  static_assert(sizeof(T) == 8 || sizeof(T) == 16, "2 or 4 words");
+  typedef unsigned w2 __attribute__((ext_vector_type(2)));
+  typedef unsigned w4 __attribute__((ext_vector_type(4)));
+  constexpr int aux = NT ? 2 : 0;
+  if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(w4, x), r, off, 0, aux);
+  else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(w2, x), r, off, 0, aux);
 }
 
 // Band-limited operands.  A load or store functor derived from `band`
@@ -294,11 +348,12 @@ __device__ __forceinline__ int fresh_tid() {
 }
 
 // One Stockham stage over a batch of NB transforms laid out at buf[t*ts + e].
-// tw[j] = exp(-2 pi i j / N) (global or LDS).
+// tw: the staged twiddles exp(-2 pi i j / N) (stage_twiddles; ROWS: as rows).
 //   load(t, e)             -> element e of transform t        (SRC_FN)
 //   store(t, e, v, it, q)  <- output element e of transform t (DST_FN*); it and q
 //                             index the caller's per-thread register arrays
-template <int N, int R, int NS, int SIGN, int NB, int NT, int SRC, int DST, typename T, class Load, class Store>
+template <int N, int R, int NS, int SIGN, int NB, int NT, int SRC, int DST, bool ROWS, typename T, class Load,
+          class Store>
 __device__ __forceinline__ void stockham_stage(T* buf, int ts, int ntrans, const T* __restrict__ tw, Load& load,
                                                Store& store) {
   constexpr int NBF = N / R;
@@ -334,7 +389,7 @@ __device__ __forceinline__ void stockham_stage(T* buf, int ts, int ntrans, const
       if constexpr (NS > 1) {
 #pragma unroll
         for (int q = 1; q < R; ++q) {
-          const T w = tw[q * k * (N / (NS * R))];
+          const T w = tw[ROWS ? k * R + q : q * k * (N / (NS * R))];
           v[it][q] = SIGN < 0 ? cmul(v[it][q], w) : cmulc(v[it][q], w);
         }
       }
@@ -351,19 +406,19 @@ __device__ __forceinline__ void stockham_stage(T* buf, int ts, int ntrans, const
   if constexpr (DST != DST_FN) __syncthreads();
 }
 
-template <int N, int NS, int SIGN, int NB, int NT, int SRC, int DST, typename T, class Load, class Store, int R,
-          int... Rest>
+template <int N, int NS, int SIGN, int NB, int NT, int SRC, int DST, bool ROWS, typename T, class Load, class Store,
+          int R, int... Rest>
 __device__ __forceinline__ void stockham_run(T* buf, int ts, int ntrans, const T* tw, Load& load, Store& store) {
   constexpr bool last = sizeof...(Rest) == 0;
-  stockham_stage<N, R, NS, SIGN, NB, NT, SRC, (last ? DST : DST_LDS), T>(buf, ts, ntrans, tw, load, store);
+  stockham_stage<N, R, NS, SIGN, NB, NT, SRC, (last ? DST : DST_LDS), ROWS, T>(buf, ts, ntrans, tw, load, store);
   if constexpr (!last)
-    stockham_run<N, NS * R, SIGN, NB, NT, SRC_LDS, DST, T, Load, Store, Rest...>(buf, ts, ntrans, tw, load, store);
+    stockham_run<N, NS * R, SIGN, NB, NT, SRC_LDS, DST, ROWS, T, Load, Store, Rest...>(buf, ts, ntrans, tw, load, store);
 }
 
 template <int N, int SIGN, int NB, int NT, int SRC, int DST, typename T, class Load, class Store, int... Rs>
 __device__ __forceinline__ void fft_io_impl(radix_list<Rs...>, T* buf, int ts, int ntrans, const T* tw, Load& load,
                                             Store& store) {
-  stockham_run<N, 1, SIGN, NB, NT, SRC, DST, T, Load, Store, Rs...>(buf, ts, ntrans, tw, load, store);
+  stockham_run<N, 1, SIGN, NB, NT, SRC, DST, sizeof...(Rs) == 2, T, Load, Store, Rs...>(buf, ts, ntrans, tw, load, store);
 }
 
 // DFT  x_k = sum_j x_j exp(SIGN 2 pi i j k / N)  of transforms t < ntrans
@@ -428,6 +483,21 @@ __device__ __forceinline__ void fft_preload_regs(FR& r, int ntrans, Load&& load)
       for (int q = 0; q < FR::radix; ++q)
         if (FR::held(q)) r.v[it][FR::slot(q)] = load(t, b + q * FR::NBF);
     }
+  }
+}
+// For every first-stage input the calling thread holds: f(item, slot,
+// transform, element); items beyond the batch get transform -1.
+template <class FR, class F>
+__device__ __forceinline__ void first_stage_positions(F&& f) {
+  constexpr int NB = FR::nb, NT = FR::nt;
+  const int tid = fresh_tid<NT>();
+#pragma unroll
+  for (int it = 0; it < FR::items; ++it) {
+    const int i = tid + it * NT;
+    const int t = (FR::TOT % NT == 0 || i < FR::TOT) ? i % NB : -1, b = i / NB;
+#pragma unroll
+    for (int q = 0; q < FR::radix; ++q)
+      if (FR::held(q)) f(it, FR::slot(q), t, b + q * FR::NBF);
   }
 }
 template <int N, int NB, int NT, typename T, bool HALF, class Load>

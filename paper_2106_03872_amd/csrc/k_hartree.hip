@@ -28,7 +28,7 @@ __global__ __launch_bounds__(NT) void hz_kernel(const double* __restrict__ rho, 
   __shared__ double2 X[HNB * (N2 + 1)];
   __shared__ double2 tw[N2];
   const int tid = threadIdx.x;
-  for (int i = tid; i < N2; i += NT) tw[i] = tw0[i];
+  stage_twiddles<N2, NT>(tw, tw0);
   const long long row0 = (long long)blockIdx.x * HNB;
   const int nr = (nrows - row0) < HNB ? (int)(nrows - row0) : HNB;
   const long long base = row0 * N2;
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(NT) void hy_kernel(double2* __restrict__ W, int n2,
   __shared__ double2 X[HNB * (N1 + 1)];
   __shared__ double2 tw[N1];
   const int tid = threadIdx.x;
-  for (int i = tid; i < N1; i += NT) tw[i] = tw0[i];
+  stage_twiddles<N1, NT>(tw, tw0);
   const int tiles = (n2 + HNB - 1) / HNB;
   const int j0 = blockIdx.x / tiles, t0 = (blockIdx.x - j0 * tiles) * HNB;
   const int nt = n2 - t0 < HNB ? n2 - t0 : HNB;
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT) void hx_kernel(double2* __restrict__ W, int n1,
   __shared__ double2 X[HNB * (N0 + 1)];
   __shared__ double2 tw[N0];
   const int tid = threadIdx.x;
-  for (int i = tid; i < N0; i += NT) tw[i] = tw0[i];
+  stage_twiddles<N0, NT>(tw, tw0);
   const int npl = n1 * n2;
   const int p0 = blockIdx.x * HNB;
   const int nt = npl - p0 < HNB ? npl - p0 : HNB;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(NT) void hzc_kernel(double2* __restrict__ W, const 
   __shared__ double2 X[HNB * (N2 + 1)];
   __shared__ double2 tw[N2];
   const int tid = threadIdx.x;
-  for (int i = tid; i < N2; i += NT) tw[i] = tw0[i];
+  stage_twiddles<N2, NT>(tw, tw0);
   const long long row0 = (long long)blockIdx.x * HNB;
   const int nr = (nrows - row0) < HNB ? (int)(nrows - row0) : HNB;
   double2* base = W + row0 * N2;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(NT) void hx_kick_kernel(double2* __restrict__ W, in
   __shared__ double2 X[HNB * (N0 + 1)];
   __shared__ double2 tw[N0];
   const int tid = threadIdx.x;
-  for (int i = tid; i < N0; i += NT) tw[i] = tw0[i];
+  stage_twiddles<N0, NT>(tw, tw0);
   const int npl = n1 * n2;
   const int p0 = blockIdx.x * HNB;
   const int nt = npl - p0 < HNB ? npl - p0 : HNB;

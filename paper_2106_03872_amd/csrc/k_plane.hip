@@ -49,7 +49,7 @@ __global__ __launch_bounds__(NTP) void plane_inv_kernel(const TIN* __restrict__ 
   }
   const int c0 = tab.plane_col0[pi], nc = tab.plane_col0[pi + 1] - c0;
   const int m1lo = tab.plane_m1lo[pi];
-  for (int i = tid; i < N; i += NTP) tw[i] = twN[i];
+  stage_twiddles<N, NTP>(tw, twN);
   for (int i = tid; i <= nc; i += NTP) s_off[i] = tab.col_off[c0 + i];
   for (int i = tid; i < nc; i += NTP) s_m2lo[i] = tab.col_m2lo[c0 + i];
   const int e0 = tab.col_off[c0], npp = tab.col_off[c0 + nc] - e0;
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(NTP) void plane_fwd_kernel(const cplx<R>* __restric
   }
   const int c0 = tab.plane_col0[pi], nc = tab.plane_col0[pi + 1] - c0;
   const int m1lo = tab.plane_m1lo[pi];
-  for (int i = tid; i < N; i += NTP) tw[i] = twN[i];
+  stage_twiddles<N, NTP>(tw, twN);
   for (int i = tid; i <= nc; i += NTP) s_off[i] = tab.col_off[c0 + i];
   for (int i = tid; i < nc; i += NTP) s_m2lo[i] = tab.col_m2lo[c0 + i];
   __syncthreads();

@@ -10,18 +10,48 @@ namespace ks {
 // x-synthesis reads T (planes m0 of each pencil) straight into its first
 // stage; LDS X[w][j0] holds one exchange buffer of the tile.
 
-template <int N0, int NB, typename C>
-struct TLoader {
-  const C* base;   // T of this orbital at the tile's first pencil
-  int npl, nplanes, m0lo, tvalid;
-  __device__ TLoader(const C* Tin, int o, int npl_, int nplanes_, int m0lo_, int p0)
-      : base(Tin + ((long long)o * nplanes_ * npl_ + p0)), npl(npl_), nplanes(nplanes_), m0lo(m0lo_),
-        tvalid(npl_ - p0) {}
-  __device__ C operator()(int t, int e) const {
-    const int pi = fold(e, N0) - m0lo;
-    return (pi >= 0 && pi < nplanes && t < tvalid) ? ld_stream(base + (unsigned)(pi * npl + t)) : czero<C>();
+// T and U of one orbital are [nplanes][npl] (npl = n1 n2 pencils).  TPos
+// gives the byte offset of element e of the tile's pencil t in that array, or
+// OOB for an element outside the sphere's planes or a pencil beyond the last
+// (buffer access then loads zero and drops stores).
+//
+// What bounds these passes: the x-tile makes two (xproj) or four (xapply)
+// trips through LDS per orbital, each behind a barrier, at three (FP64) or
+// four (complex64) waves per SIMD, so the SIMDs alternate between issue and
+// waiting, and every instruction beside the transform's own counts.  With
+// per-element branches, zero fills and 64-bit addresses the orbital loop of
+// xproj had 131 integer and 170 scalar instructions beside 276 FP64 ones; it
+// has 108 and 50.  Measured together with the projection reads in groups and
+// the twiddle rows, per launch before and after: 96^3 / 512 orbitals FP64
+// xproj 964 and 875 us, xapply 1543 and 1451 us (4.2 and 4.5 TB/s); complex64
+// xapply 1074 and 987 us; 120^3 / 1024 complex64 xproj 2758 and 2502 us, xapply
+// 4592 and 4377 us.
+template <int N0, typename C>
+struct TPos {
+  int npl, nplanes, m0lo, p0;
+  static constexpr unsigned BEYOND = 0x40000000u;   // past every array, also after adding a plane's offset
+  __device__ TPos(const SphereTab& tab, int p0_) : npl(tab.n1 * tab.n2), nplanes(tab.nplanes), m0lo(tab.m0lo), p0(p0_) {}
+  __device__ __forceinline__ unsigned bytes() const { return (unsigned)(nplanes * npl) * sizeof(C); }
+  __device__ __forceinline__ unsigned pencil(int t) const {
+    return t >= 0 && p0 + t < npl ? (unsigned)(p0 + t) * sizeof(C) : BEYOND;
   }
+  // plane pi of the pencil at byte offset pb
+  __device__ __forceinline__ unsigned plane(unsigned pb, int pi) const {
+    const unsigned off = pb + (unsigned)__mul24(pi, npl * (int)sizeof(C));
+    return (unsigned)pi < (unsigned)nplanes ? off : OOB;
+  }
+  __device__ __forceinline__ unsigned operator()(int t, int e) const { return plane(pencil(t), fold(e, N0) - m0lo); }
 };
+
+// Issue the loads of a thread's first-stage inputs of one orbital (T of
+// `bytes` bytes) into r.  The offsets are formed anew for each orbital (four
+// instructions per element): kept across orbitals they take the FP64 passes
+// past the 168 registers of three waves per SIMD.
+template <class FR, int N0, typename C>
+__device__ __forceinline__ void load_inputs(FR& r, const TPos<N0, C>& pos, const C* T, unsigned bytes) {
+  const gbuf b = make_gbuf(T, bytes);
+  first_stage_positions<FR>([&](int it, int s, int t, int e) { r.v[it][s] = buf_load<C, true>(b, pos(t, e)); });
+}
 
 // x from another lane of the same row of 16 by the DPP permutation CTRL
 // (quad_perm, row_half_mirror, row_mirror: every source lane is in the row)
@@ -77,9 +107,17 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
   }
   const int npl = tab.n1 * tab.n2;
   const int p0 = tile * NB;
+  // the block's first loads, independent of each other, are issued together:
+  // the first orbital, the work item, the slot range, the twiddles
+  const TPos<N0, C> pos(tab, p0);
+  const unsigned tbytes = pos.bytes();
+  const long long tstride = (long long)tab.nplanes * npl;
+  FR pre;
+  if (oa < ob) load_inputs(pre, pos, Tin + oa * tstride, tbytes);
+  const int4 item = pt.item[(long long)tile * XT + tid];
   const int sA = pt.slot_off[tile], ns = pt.slot_off[tile + 1] - sA;
   if (!DENS && ns == 0) return;  // no sphere point in this tile (uniform per block)
-  for (int i = tid; i < N0; i += XT) tw[i] = tw0[i];
+  stage_twiddles<N0, XT, SH::V>(tw, tw0);
   double a[DENS ? LS::items : 1][DENS ? LS::radix : 1];
   if constexpr (DENS) {
 #pragma unroll
@@ -93,31 +131,50 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
   // group's first lane writes the pair (work planned per tile on the host).
   // (the host plans XT projection lanes per tile)
   const int np = pt.nproj;
-  const int4 item = pt.item[(long long)tile * XT + tid];
   const int ka = item.x, kb = item.y;
   const int sl = item.z / np, kq = item.z - sl * np;
   const int glanes = 1 << (item.w & 0xff);
   const bool writer = (item.w & 256) != 0;
   // The first KP points of the item (LDS position, beta) are the same for
   // all orbitals of the block and stay in registers.
-  constexpr int KP = KB_CACHED_POINTS;
+  // Points a lane lacks read the unused last word of the first pencil's row
+  // (zero) with beta = 0, so that the reads of KPG points are in flight
+  // together instead of one behind each lane's own bound; groups that no lane
+  // of the wave has are skipped.
+  constexpr int KP = KB_CACHED_POINTS, KPG = 4;
+  static_assert(KP % KPG == 0, "whole groups");
   int cpos[KP];
   double cbeta[KP];
+  if (tid == 0) X[N0] = czero<C>();
+  const int k0 = DENS && ns == 0 ? 0 : pt.slot_pt[sA];   // a row of the tile
 #pragma unroll
-  for (int c = 0; c < KP; ++c) {
-    const int k = ka + c;
-    const bool in = k < kb;
-    cpos[c] = in ? pt.pt_lds[k] : 0;
-    cbeta[c] = in ? pt.beta[(long long)k * np + kq] : 0.0;
+  for (int g = 0; g < KP; g += KPG) {
+    if (__any(ka + g < kb)) {
+#pragma unroll
+      for (int c = g; c < g + KPG; ++c) {
+        const int k = ka + c < kb ? ka + c : k0;
+        cpos[c] = pt.pt_lds[k];
+        cbeta[c] = pt.beta[(long long)k * np + kq];
+      }
+    } else {
+#pragma unroll
+      for (int c = g; c < g + KPG; ++c) {
+        cpos[c] = 0;
+        cbeta[c] = 0.0;
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < KP; ++c) {   // after all loads are issued
+    const bool in = ka + c < kb;
+    cpos[c] = in ? cpos[c] : N0;
+    cbeta[c] = in ? cbeta[c] : 0.0;
   }
   C* pout = partial + (long long)(sA + sl) * np + kq;
   const long long pstride = (long long)pt.nslots * np;
-  FR pre;
-  if (oa < ob) fft_preload_regs(pre, NB, TLoader<N0, NB, C>(Tin, oa, npl, tab.nplanes, tab.m0lo, p0));
   for (int o = oa; o < ob; ++o) {
     auto next = [&] {
-      if (o + 1 < ob)
-        fft_preload_regs(pre, NB, TLoader<N0, NB, C>(Tin, o + 1, npl, tab.nplanes, tab.m0lo, p0));
+      if (o + 1 < ob) load_inputs(pre, pos, Tin + (o + 1) * tstride, tbytes);
     };
     if constexpr (DENS) {
       const double f = occ[o] * inv_omega;
@@ -135,11 +192,16 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
     }
     double sx = 0.0, sy = 0.0;
 #pragma unroll
-    for (int c = 0; c < KP; ++c) {
-      if (ka + c < kb) {
-        const C x = X[cpos[c]];
-        sx += cbeta[c] * double(x.x);
-        sy += cbeta[c] * double(x.y);
+    for (int g = 0; g < KP; g += KPG) {
+      if (__any(ka + g < kb)) {
+        C x[KPG];
+#pragma unroll
+        for (int c = 0; c < KPG; ++c) x[c] = X[cpos[g + c]];
+#pragma unroll
+        for (int c = 0; c < KPG; ++c) {
+          sx += cbeta[g + c] * double(x[c].x);
+          sy += cbeta[g + c] * double(x[c].y);
+        }
       }
     }
     for (int k = ka + KP; k < kb; ++k) {
@@ -216,20 +278,30 @@ __device__ __forceinline__ void kb_extra(const double2* dps, const ProjTab& pt, 
 // NP projectors per atom fixed at compile time: two unique points per thread
 // and pass, u and u + XT, with the table loads of both issued before either
 // is used.
+//
+// A grid has at most 128^3 unique points of at most 8 projectors, so 32-bit
+// byte offsets reach every row of the tables.
+template <typename T>
+__device__ __forceinline__ const T* row32(const T* base, unsigned index, unsigned row) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (index * row * (unsigned)sizeof(T)));
+}
 template <int NP, int XT, typename C>
 __device__ __forceinline__ void kb_scatter_fixed(C* X, const double2* dps, const ProjTab& pt, int uA, int uB) {
   const int tid = threadIdx.x;
   for (int u = uA + tid; u < uB; u += 2 * XT) {
-    const int ub = u + XT;
-    const bool two = ub < uB;
-    const int ka = pt.up_key[u];
-    const int kb = two ? pt.up_key[ub] : 0;
+    const bool two = u + XT < uB;
+    const int ub = two ? u + XT : u;
+    const int ka = *row32(pt.up_key, u, 1);
+    const int kb = *row32(pt.up_key, ub, 1);
+    const double* rowa = row32(pt.up_beta, u, NP);
+    const double* rowb = row32(pt.up_beta, ub, NP);
     double ba[NP], bb[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-      ba[q] = pt.up_beta[(long long)u * NP + q];
-      bb[q] = two ? pt.up_beta[(long long)ub * NP + q] : 0.0;
+      ba[q] = rowa[q];
+      bb[q] = rowb[q];
     }
+    __builtin_amdgcn_sched_barrier(0);   // no use of a key before the rows' loads are issued
     const double2* da = dps + ((ka >> UP_POS_BITS) & UP_MAX_SLOT) * NP;
     const double2* db = dps + ((kb >> UP_POS_BITS) & UP_MAX_SLOT) * NP;
     double ax = 0.0, ay = 0.0, bx = 0.0, by = 0.0;
@@ -298,9 +370,13 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
   } else {
     orbital_range(nb, oa, ob);
   }
-  for (int i = tid; i < N0; i += XT) tw[i] = tw0[i];
   const int npl = tab.n1 * tab.n2;
   const int p0 = tile * NB;
+  const TPos<N0, C> pos(tab, p0);
+  const unsigned tbytes = pos.bytes();
+  const long long tstride = (long long)tab.nplanes * npl;
+  FR pre;
+  if (oa < ob) load_inputs(pre, pos, Tin + oa * tstride, tbytes);
   // potential at the outputs of this thread's last synthesis stage, times the
   // synthesis and analysis scales Omega^-1/2 Omega^1/2 / N = 1/N
   double vr[LS::items][LS::radix];
@@ -320,10 +396,7 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
     dp_off = (long long)pt.slot_atom[sA + sl] * np + q;
   }
   const int uA = pt.up_off[tile], uB = pt.up_off[tile + 1];
-  const int nplanes = tab.nplanes, m0lo = tab.m0lo;
-  const int tvalid = npl - p0;
-  FR pre;
-  if (oa < ob) fft_preload_regs(pre, NB, TLoader<N0, NB, C>(Tin, oa, npl, nplanes, m0lo, p0));
+  stage_twiddles<N0, XT, SH::V>(tw, tw0);
   double2 dnext = {0.0, 0.0};
   if (tid < ndp && oa < ob) dnext = DP[oa * dp_stride + dp_off];
   for (int o = oa; o < ob; ++o) {
@@ -332,7 +405,7 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
     if (tid < ndp) dps[tid] = dnext;
     auto next = [&] {
       if (o + 1 < ob) {
-        fft_preload_regs(pre, NB, TLoader<N0, NB, C>(Tin, o + 1, npl, nplanes, m0lo, p0));
+        load_inputs(pre, pos, Tin + (o + 1) * tstride, tbytes);
         if (tid < ndp) dnext = DP[(o + 1) * dp_stride + dp_off];
       }
     };
@@ -345,10 +418,17 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
       else kb_scatter_any<XT>(X, dps, pt, uA, uB);
       __syncthreads();
     }
-    C* obase = Uout + (long long)o * nplanes * npl + p0;
-    auto store = [&](int t, int e, C v, int, int) {
-      const int pi = fold(e, N0) - m0lo;
-      if (pi >= 0 && pi < nplanes && t < tvalid) st_stream(obase + (unsigned)(pi * npl + t), v);
+    // The stores stay behind branches: the compiler then rounds the last
+    // butterfly's products before their sums.  Without the branches it fuses
+    // some of them, and the complex64 results change in their last bits from
+    // one plan to the next.
+    const gbuf ub = make_gbuf(Uout + o * tstride, tbytes);
+    auto store = [&](int t, int e, C v, int, int q) {
+      // in the band the frequency of output q follows from q alone
+      const int m0 = HB && LS::radix % 4 == 0 ? (q < LS::radix / 4 ? e : e - N0) : fold(e, N0);
+      const int pi = m0 - pos.m0lo;
+      if (pi >= 0 && pi < pos.nplanes && p0 + t < npl)
+        buf_store<true>(ub, (unsigned)((p0 + t) * (int)sizeof(C) + __mul24(pi, npl * (int)sizeof(C))), v);
     };
     // only the sphere's planes are stored; with HB they all lie in the band |m0| < n0/4
     if constexpr (HB) fft_io<N0, -1, NB, XT, SRC_LDS, DST_FN, C, SH::V>(X, N0 + 1, NB, tw, no_load{}, banded(store));
@@ -361,8 +441,9 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
 // straight from the last synthesis stage over the group's orbitals in order
 // and written to the group's partial density; dens_sum adds the groups in
 // order.
+// (The band-limited FP64 form is held to the 168 registers of three waves per SIMD.)
 template <int N0, class SH, typename R, bool HB>
-__global__ __launch_bounds__(SH::XT) void xdens_kernel(const cplx<R>* __restrict__ Tin, int nb,
+__global__ __launch_bounds__(SH::XT) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && HB ? 3 : 1))) void xdens_kernel(const cplx<R>* __restrict__ Tin, int nb,
                                                    const double* __restrict__ occ, double* __restrict__ part,
                                                    SphereTab tab, const cplx<R>* __restrict__ tw0,
                                                    double inv_omega) {
@@ -374,7 +455,7 @@ __global__ __launch_bounds__(SH::XT) void xdens_kernel(const cplx<R>* __restrict
   const int tile = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
   const int npl = tab.n1 * tab.n2;
   const int p0 = tile * NB;
-  for (int i = tid; i < N0; i += XT) tw[i] = tw0[i];
+  stage_twiddles<N0, XT, SH::V>(tw, tw0);
   double a[LS::items][LS::radix];
 #pragma unroll
   for (int it = 0; it < LS::items; ++it)
@@ -384,12 +465,14 @@ __global__ __launch_bounds__(SH::XT) void xdens_kernel(const cplx<R>* __restrict
   orbital_range(nb, oa, ob);
   // the next orbital's T is loaded once the first stage has consumed the current one
   using FR = fft_regs<N0, NB, XT, C, HB, SH::V>;
+  const TPos<N0, C> pos(tab, p0);
+  const unsigned tbytes = pos.bytes();
+  const long long tstride = (long long)tab.nplanes * npl;
   FR pre;
-  if (oa < ob) fft_preload_regs(pre, NB, TLoader<N0, NB, C>(Tin, oa, npl, tab.nplanes, tab.m0lo, p0));
+  if (oa < ob) load_inputs(pre, pos, Tin + oa * tstride, tbytes);
   for (int o = oa; o < ob; ++o) {
     auto next = [&] {
-      if (o + 1 < ob)
-        fft_preload_regs(pre, NB, TLoader<N0, NB, C>(Tin, o + 1, npl, tab.nplanes, tab.m0lo, p0));
+      if (o + 1 < ob) load_inputs(pre, pos, Tin + (o + 1) * tstride, tbytes);
     };
     const double f = occ[o] * inv_omega;
     fft_io<N0, +1, NB, XT, SRC_PRE, DST_FN, C, SH::V>(X, N0 + 1, NB, tw, preloaded(pre, next), [&](int, int, C v, int it, int q) {
