@@ -279,8 +279,18 @@ __device__ __forceinline__ void st_stream(T* p, T x) {
 // offset set to OOB.  Accesses stream past L2 (non-temporal) or not by NT.
 typedef __amdgpu_buffer_rsrc_t gbuf;
 constexpr unsigned OOB = 0x7ffffff0u;   // beyond every buffer (arrays here are below 2^30 bytes)
+// A pointer that is the same for the whole block, held in scalar registers
+// (the compiler forms 64-bit products in vector registers and would otherwise
+// move the address over at every access).
+template <typename T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const unsigned long long b = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)b);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
+  return reinterpret_cast<T*>((unsigned long long)hi << 32 | lo);
+}
 __device__ __forceinline__ gbuf make_gbuf(const void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(uniform_ptr(base)), 0, (int)bytes, 0x00020000);
 }
 template <typename T, bool NT = false>
 __device__ __forceinline__ T buf_load(gbuf r, unsigned off) {

@@ -975,12 +975,21 @@ static ks_status system_create(ks_pool* pool, const int n[3], const double L[3],
     return st;
   }
   {
-    // |G|^2/2 of each packed coefficient (preconditioner of the eigensolver)
+    // |G|^2/2 of each packed coefficient (kinetic term of the plane analysis,
+    // preconditioner of the eigensolver), with the roundings of a fused
+    // multiply-add chain
+    const double g0 = 2.0 * M_PI / L[0], g1 = 2.0 * M_PI / L[1], g2 = 2.0 * M_PI / L[2];
     std::vector<double> kp((size_t)npw);
-    for (int pi = 0; pi < s->nplanes; ++pi)
-      for (int c = plane_col0[pi]; c < plane_col0[pi + 1]; ++c)
-        for (int e = col_off[c]; e < col_off[c + 1]; ++e)
-          kp[e] = kin(L, s->m0lo + pi, plane_m1lo[pi] + (c - plane_col0[pi]), col_m2lo[c] + (e - col_off[c]));
+    for (int pi = 0; pi < s->nplanes; ++pi) {
+      const double k0 = g0 * (s->m0lo + pi);
+      for (int c = plane_col0[pi]; c < plane_col0[pi + 1]; ++c) {
+        const double k1 = g1 * (plane_m1lo[pi] + (c - plane_col0[pi])), k01 = std::fma(k1, k1, k0 * k0);
+        for (int e = col_off[c]; e < col_off[c + 1]; ++e) {
+          const double k2 = g2 * (col_m2lo[c] + (e - col_off[c]));
+          kp[e] = 0.5 * std::fma(k2, k2, k01);
+        }
+      }
+    }
     if ((st = upload(s, &s->d_kin, kp)) != KS_OK) {
       g_create_err = s->err;
       ks_system_destroy(s);

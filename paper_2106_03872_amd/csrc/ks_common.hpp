@@ -12,7 +12,6 @@ constexpr int DENS_GROUP = 8;   // smallest orbital group of a density block
 
 // pencils per x-tile (host side: x_tile_nb)
 template <int N> struct xnb { static constexpr int value = N <= 32 ? 64 : 32; };
-constexpr int NTP = 384; // threads per plane-pass block
 
 template <typename T> __device__ __forceinline__ T czero() { return T{0, 0}; }
 
@@ -36,7 +35,6 @@ __device__ __forceinline__ int find_col(const int* off, int nc, int e) {
 }
 
 
-template <int N> struct pnb { static constexpr int value = N <= 64 ? 64 : (N <= 96 ? 48 : (N <= 120 ? 24 : 16)); };
 
 inline bool mixed(const ks_system* s) { return s->prec == KS_MIXED; }
 

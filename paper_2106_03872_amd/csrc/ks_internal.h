@@ -146,7 +146,7 @@ struct ks_system {
   // static V_loc
   double* d_v = nullptr;
   double* d_vloc = nullptr;
-  double* d_kin = nullptr;   // |G|^2/2 of each packed coefficient [npw]
+  double* d_kin = nullptr;   // |G|^2/2 of each packed coefficient [npw] (kinetic term, preconditioner)
   bool have_v = false;
   // Hartree solve: complex work box [n0][n1][n2] and a density [n0][n1][n2]
   double2* d_hbox = nullptr;
