@@ -41,30 +41,43 @@ __global__ __launch_bounds__(NT) void pack_kernel(const double2* __restrict__ bo
   }
 }
 
-template <typename T>
+// Block (box plane j0, orbital): planes outside the sphere are a plain fill;
+// in a plane of the sphere a thread finds its element's column in the plane's
+// tables (in LDS).  Bound: HBM writes of the box.  One thread per element of
+// the whole box, with its indices divided out of a 64-bit position and five
+// dependent table loads, wrote 3.9 TB/s at 96^3 / 512 orbitals (1830 us); this
+// form writes 5.0 TB/s (1450 us; 64^3 / 128: 148 and 108 us; 120^3 / 1024: 7080
+// and 5890 us).
+template <int N, typename T>
 __global__ __launch_bounds__(NT) void unpack_kernel(const T* __restrict__ pk, int pk_stride,
                                                     double2* __restrict__ box, long long box_stride,
                                                     SphereTab tab) {
-  const long long N = (long long)tab.n0 * tab.n1 * tab.n2;
-  const long long bi = (long long)blockIdx.x * NT + threadIdx.x;
-  if (bi >= N) return;
-  const int o = blockIdx.y;
-  const int j2 = bi % tab.n2;
-  const int j1 = (bi / tab.n2) % tab.n1;
-  const int j0 = bi / ((long long)tab.n1 * tab.n2);
-  double2 v{0.0, 0.0};
+  __shared__ int s_off[130];
+  __shared__ int s_m2lo[129];
+  const int j0 = blockIdx.x, tid = threadIdx.x;
+  const long long o = blockIdx.y;
+  double2* out = box + o * box_stride + (long long)j0 * (N * N);
   const int pi = fold(j0, tab.n0) - tab.m0lo;
-  if (pi >= 0 && pi < tab.nplanes) {
-    const int c = fold(j1, tab.n1) - tab.plane_m1lo[pi];
-    const int c0 = tab.plane_col0[pi];
-    if (c >= 0 && c < tab.plane_col0[pi + 1] - c0) {
-      const int cc = c0 + c;
-      const int t = fold(j2, tab.n2) - tab.col_m2lo[cc];
-      const int off = tab.col_off[cc];
-      if (t >= 0 && t < tab.col_off[cc + 1] - off) v = to_d(pk[(long long)o * pk_stride + off + t]);
-    }
+  if (pi < 0 || pi >= tab.nplanes) {
+#pragma unroll 4
+    for (int i = tid; i < N * N; i += NT) st_stream(out + i, double2{0.0, 0.0});
+    return;
   }
-  box[(long long)o * box_stride + bi] = v;
+  const int c0 = tab.plane_col0[pi], nc = tab.plane_col0[pi + 1] - c0, m1lo = tab.plane_m1lo[pi];
+  for (int i = tid; i <= nc; i += NT) s_off[i] = tab.col_off[c0 + i];
+  for (int i = tid; i < nc; i += NT) s_m2lo[i] = tab.col_m2lo[c0 + i];
+  __syncthreads();
+  const T* in = pk + o * pk_stride;
+  for (int i = tid; i < N * N; i += NT) {
+    const int j1 = i / N, j2 = i - j1 * N;
+    const int c = fold(j1, N) - m1lo;
+    double2 v{0.0, 0.0};
+    if (c >= 0 && c < nc) {
+      const int t = fold(j2, N) - s_m2lo[c], off = s_off[c];
+      if (t >= 0 && t < s_off[c + 1] - off) v = to_d(in[off + t]);
+    }
+    st_stream(out + i, v);
+  }
 }
 
 // KB projections: P_Ip = sum over the (tile, atom) slots of atom I in
@@ -112,46 +125,75 @@ __global__ __launch_bounds__(64) void proj_reduce_kernel(const C* __restrict__ p
   }
 }
 
-// per-orbital sums over the packed sphere: out[2o] = sum |a|^2, out[2o+1] = sum Re conj(a) b
+// sum over the lanes of a wave (a fixed butterfly: every lane gets the sum)
+__device__ __forceinline__ double wave_sum(double x) {
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) x += __shfl_xor(x, m, 64);
+  return x;
+}
+
+// per-orbital sums over the packed sphere: out[2o] = sum |a|^2, out[2o+1] =
+// sum Re conj(a) b; norms (nullable): norms[o] = sum |a|^2 as well.
+// Bound: HBM reads of the orbitals.  A block of 256 threads with one load in
+// flight per thread took 15.7 us for 128 orbitals at 64^3 and 90 us for 512
+// at 96^3 (3.7 TB/s), and the norms were gathered by a strided copy of 4 us;
+// 512 threads with four loads each take 6.4 and 57 us.
+constexpr int NT_DOT = 512, DOT_U = 4;
 template <typename CA, typename CB_>
-__global__ __launch_bounds__(NT) void dots_kernel(const CA* __restrict__ a, const CB_* __restrict__ b, int stride,
-                                                  int npw, double* __restrict__ out) {
-  __shared__ double s0[NT], s1[NT];
+__global__ __launch_bounds__(NT_DOT) void dots_kernel(const CA* __restrict__ a, const CB_* __restrict__ b, int stride,
+                                                      int npw, double* __restrict__ out, double* __restrict__ norms) {
+  __shared__ double s0[NT_DOT / 64], s1[NT_DOT / 64];
   const int o = blockIdx.x, tid = threadIdx.x;
   const CA* pa = a + (long long)o * stride;
   const CB_* pb = b ? b + (long long)o * stride : nullptr;
-  double x0 = 0.0, x1 = 0.0;
-  for (int e = tid; e < npw; e += NT) {
-    const CA u = pa[e];
-    x0 += double(u.x) * double(u.x) + double(u.y) * double(u.y);
+  double x0[DOT_U], x1[DOT_U];
+#pragma unroll
+  for (int j = 0; j < DOT_U; ++j) x0[j] = x1[j] = 0.0;
+  for (int e0 = tid; e0 < npw; e0 += DOT_U * NT_DOT) {
+    CA u[DOT_U];
+#pragma unroll
+    for (int j = 0; j < DOT_U; ++j) {
+      const int e = e0 + j * NT_DOT;
+      u[j] = e < npw ? pa[e] : CA{0, 0};
+    }
+#pragma unroll
+    for (int j = 0; j < DOT_U; ++j) x0[j] += double(u[j].x) * double(u[j].x) + double(u[j].y) * double(u[j].y);
     if (pb) {
-      const CB_ v = pb[e];
-      x1 += double(u.x) * double(v.x) + double(u.y) * double(v.y);
+      CB_ v[DOT_U];
+#pragma unroll
+      for (int j = 0; j < DOT_U; ++j) {
+        const int e = e0 + j * NT_DOT;
+        v[j] = e < npw ? pb[e] : CB_{0, 0};
+      }
+#pragma unroll
+      for (int j = 0; j < DOT_U; ++j) x1[j] += double(u[j].x) * double(v[j].x) + double(u[j].y) * double(v[j].y);
     }
   }
-  s0[tid] = x0;
-  s1[tid] = x1;
+  const double y0 = wave_sum((x0[0] + x0[1]) + (x0[2] + x0[3])), y1 = wave_sum((x1[0] + x1[1]) + (x1[2] + x1[3]));
+  if ((tid & 63) == 0) {
+    s0[tid >> 6] = y0;
+    s1[tid >> 6] = y1;
+  }
   __syncthreads();
-  for (int h = NT / 2; h > 0; h >>= 1) {
-    if (tid < h) {
-      s0[tid] += s0[tid + h];
-      s1[tid] += s1[tid + h];
-    }
-    __syncthreads();
-  }
   if (tid == 0) {
-    out[2 * o] = s0[0];
-    out[2 * o + 1] = s1[0];
+    double t0 = 0.0, t1 = 0.0;
+    for (int w = 0; w < NT_DOT / 64; ++w) {
+      t0 += s0[w];
+      t1 += s1[w];
+    }
+    out[2 * o] = t0;
+    out[2 * o + 1] = t1;
+    if (norms) norms[o] = t0;
   }
 }
 
-__global__ void energy_sum_kernel(int norb, const double* __restrict__ occ, const double* __restrict__ red,
-                                  double* __restrict__ energy) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double e = 0.0;
-    for (int o = 0; o < norb; ++o) e += occ[o] * red[2 * o + 1];
-    energy[0] = e;
-  }
+// energy = sum_o occ[o] red[2o+1], in a fixed order (one wave)
+__global__ __launch_bounds__(64) void energy_sum_kernel(int norb, const double* __restrict__ occ,
+                                                        const double* __restrict__ red, double* __restrict__ energy) {
+  double e = 0.0;
+  for (int o = threadIdx.x; o < norb; o += 64) e += occ[o] * red[2 * o + 1];
+  e = wave_sum(e);
+  if (threadIdx.x == 0) energy[0] = e;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -164,14 +206,20 @@ bool launch_pack(const ks_system* s, int nb, const double2* box, long long box_s
 
 bool launch_unpack(const ks_system* s, int nb, const void* pk, bool pk_fp64, double2* box, long long box_stride,
                    hipStream_t st) {
-  const unsigned gx = (unsigned)((s->N + NT - 1) / NT);
-  if (pk_fp64)
-    unpack_kernel<double2><<<dim3(gx, nb), NT, 0, st>>>((const double2*)pk, s->npw_stride, box, box_stride,
-                                                         sphere_tab(s));
-  else
-    unpack_kernel<float2><<<dim3(gx, nb), NT, 0, st>>>((const float2*)pk, s->npw_stride, box, box_stride,
-                                                        sphere_tab(s));
-  return true;
+  const dim3 grid(s->n[0], nb);
+  switch (s->n[1]) {
+#define KS_CASE(v)                                                                                               \
+  case v:                                                                                                        \
+    if (pk_fp64)                                                                                                 \
+      unpack_kernel<v, double2><<<grid, NT, 0, st>>>((const double2*)pk, s->npw_stride, box, box_stride, sphere_tab(s)); \
+    else                                                                                                         \
+      unpack_kernel<v, float2><<<grid, NT, 0, st>>>((const float2*)pk, s->npw_stride, box, box_stride, sphere_tab(s)); \
+    return true;
+    KS_SIZES(KS_CASE)
+#undef KS_CASE
+    default:
+      return false;
+  }
 }
 
 bool launch_proj_reduce(const ks_system* s, int nb, const void* partial, double2* DP, hipStream_t st) {
@@ -198,13 +246,13 @@ bool launch_proj_reduce_batch(const ks_system* s, const BatchJob* jobs, const in
 }
 
 // a: the FP64 state; b: H applied to it in the working precision (or null)
-bool launch_dots(const ks_system* s, int nb, const void* a, const void* b, double* out, hipStream_t st) {
+bool launch_dots(const ks_system* s, int nb, const void* a, const void* b, double* out, double* norms, hipStream_t st) {
   if (!mixed(s))
-    dots_kernel<double2, double2><<<nb, NT, 0, st>>>((const double2*)a, (const double2*)b, s->npw_stride, s->npw,
-                                                     out);
+    dots_kernel<double2, double2><<<nb, NT_DOT, 0, st>>>((const double2*)a, (const double2*)b, s->npw_stride, s->npw,
+                                                         out, norms);
   else
-    dots_kernel<double2, float2><<<nb, NT, 0, st>>>((const double2*)a, (const float2*)b, s->npw_stride, s->npw,
-                                                    out);
+    dots_kernel<double2, float2><<<nb, NT_DOT, 0, st>>>((const double2*)a, (const float2*)b, s->npw_stride, s->npw,
+                                                        out, norms);
   return true;
 }
 

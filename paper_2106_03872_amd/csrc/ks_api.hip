@@ -596,12 +596,10 @@ ks_status taylor_packed(ks_system* s, int nb, double2* state, double dt, int nst
     if (rho && (!fuse || step == nsteps - 1) &&
         (r = density_packed(s, nb, state, occ, rho + (size_t)step * s->N, accumulate, st)) != KS_OK)
       return r;
-    if (norms) {
-      if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] { return launch_dots(s, nb, state, nullptr, s->red, st); })) != KS_OK)
-        return r;
-      KS_HIP(s, hipMemcpy2DAsync(norms + (size_t)step * norms_stride, sizeof(double), s->red, 2 * sizeof(double),
-                                 sizeof(double), nb, hipMemcpyDeviceToDevice, st));
-    }
+    if (norms && (r = kcall(s, KS_K_DOTS, st, "dots", [&] {
+           return launch_dots(s, nb, state, nullptr, s->red, norms + (size_t)step * norms_stride, st);
+         })) != KS_OK)
+      return r;
   }
   return KS_OK;
 }
@@ -683,10 +681,10 @@ ks_status etrs_packed(ks_system* s, ks_state* t, double dt, int nsteps, const do
       for (int o0 = 0; o0 < t->norb; o0 += cl) {
         const int nb = std::min(cl, t->norb - o0);
         const double2* slice = t->data + (size_t)o0 * s->npw_stride;
-        if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] { return launch_dots(s, nb, slice, nullptr, s->red, st); })) != KS_OK)
+        if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] {
+               return launch_dots(s, nb, slice, nullptr, s->red, norms + (size_t)step * t->norb + o0, st);
+             })) != KS_OK)
           return r;
-        KS_HIP(s, hipMemcpy2DAsync(norms + (size_t)step * t->norb + o0, sizeof(double), s->red, 2 * sizeof(double),
-                                   sizeof(double), nb, hipMemcpyDeviceToDevice, st));
       }
     }
     if (step + 1 < nsteps && (r = update_potential(s, st)) != KS_OK) return r;
@@ -1486,12 +1484,10 @@ ks_status ks_reduce(ks_system* s, int norb, const void* psi, const double* occ, 
     if (energy && (r = hpsi_packed(s, nb, s->pk[0], true, s->pk[1], nullptr, H_OUT, none, st)) != KS_OK) return r;
     const void* hp = energy ? s->pk[1] : nullptr;
     double* red = s->red + 2 * (size_t)o0;
-    if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] { return launch_dots(s, nb, s->pk[0], hp, red, st); })) != KS_OK)
+    if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] { return launch_dots(s, nb, s->pk[0], hp, red, norms ? norms + o0 : nullptr, st); })) !=
+        KS_OK)
       return r;
   }
-  if (norms)
-    KS_HIP(s, hipMemcpy2DAsync(norms, sizeof(double), s->red, 2 * sizeof(double), sizeof(double), norb,
-                               hipMemcpyDeviceToDevice, st));
   if (energy) return kcall(s, KS_K_DOTS, st, "energy_sum", [&] { return launch_energy_sum(norb, occ, s->red, energy, st); });
   return KS_OK;
 }
@@ -1816,12 +1812,10 @@ ks_status ks_state_reduce(ks_state* t, const double* occ, double* norms, double*
     if (energy && (r = hpsi_packed(s, nb, slice, true, s->pk[1], nullptr, H_OUT, none, st)) != KS_OK) return r;
     const void* hp = energy ? s->pk[1] : nullptr;
     double* red = s->red + 2 * (size_t)o0;
-    if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] { return launch_dots(s, nb, slice, hp, red, st); })) != KS_OK)
+    if ((r = kcall(s, KS_K_DOTS, st, "dots", [&] { return launch_dots(s, nb, slice, hp, red, norms ? norms + o0 : nullptr, st); })) !=
+        KS_OK)
       return r;
   }
-  if (norms)
-    KS_HIP(s, hipMemcpy2DAsync(norms, sizeof(double), s->red, 2 * sizeof(double), sizeof(double), t->norb,
-                               hipMemcpyDeviceToDevice, st));
   if (energy)
     return kcall(s, KS_K_DOTS, st, "energy_sum", [&] { return launch_energy_sum(t->norb, occ, s->red, energy, st); });
   return KS_OK;

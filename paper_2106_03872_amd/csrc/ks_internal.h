@@ -302,7 +302,8 @@ bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4
 // total_orbitals orbitals (the same rule as the single-system launches)
 int x_group_size(const ks_system* s, long long total_orbitals);
 int plane_group_size(const ks_system* s, long long total_orbitals);
-bool launch_dots(const ks_system* s, int nb, const void* a, const void* b, double* out, hipStream_t st);
+// norms (nullable): the sums |a|^2 also in a contiguous array
+bool launch_dots(const ks_system* s, int nb, const void* a, const void* b, double* out, double* norms, hipStream_t st);
 bool launch_energy_sum(int norb, const double* occ, const double* red, double* energy, hipStream_t st);
 // part: split-K partial products (part_bytes of them; NULL: no split)
 bool launch_overlap(int norb, int npw, const double2* P, int ldp, double2* S, double2* part, size_t part_bytes,
