@@ -42,8 +42,9 @@ __device__ __forceinline__ void round_pair(int t, int k, int m, int& p, int& q) 
 
 constexpr int BJ_B = 16;            // index block
 constexpr int BJ_M = 2 * BJ_B;      // sub-problem order
-constexpr int BJ_NT = 256;
-static_assert(BJ_B * BJ_B == BJ_NT, "one thread per 2x2 block of a sub-problem");
+constexpr int BJ_NT = 256;          // threads of an apply block
+constexpr int BJ_ST = 512;          // threads of a solve block: one half works on S, the other on U
+static_assert(2 * BJ_B * BJ_B == BJ_ST, "one thread per 2x2 block of S and one per 2x2 of U");
 
 // Rotation J (2x2, acting on indices p < q) with (J^H A J)_pq = 0 for the
 // Hermitian block [[a, b], [conj(b), c]]: with b = |b| e^{i phi}, the phase
@@ -52,8 +53,8 @@ static_assert(BJ_B * BJ_B == BJ_NT, "one thread per 2x2 block of a sub-problem")
 // t^2 + 2 tau t - 1 = 0, tau = (c - a) / (2|b|), zeroes it; J = D R, i.e.
 //   J = [[cs, sn], [-f, g]],  f = sn e, g = cs e,  e = e^{-i phi}.
 // With h = |tau| + sqrt(1 + tau^2) = 1/|t|: cs = h / sqrt(1 + h^2) and
-// sn = sign(tau) / sqrt(1 + h^2), so the chain has two reciprocal square
-// roots and one square root and no division.  An element so small against
+// sn = sign(tau) / sqrt(1 + h^2), with sqrt(x) = x rsqrt(x) for x >= 1, so the
+// chain has three reciprocal square roots and no division.  An element so small against
 // the diagonal gap that h^2 would overflow is left alone (the rotation angle
 // would be below 1e-150).
 struct Rot {
@@ -69,7 +70,8 @@ __device__ __forceinline__ Rot make_rot(double a, double c, double2 b) {
   const double tau = 0.5 * (c - a) * rb;
   const double at = fabs(tau);
   if (!(at < 1e150)) return r;
-  const double h = at + sqrt(fma(tau, tau, 1.0));
+  const double q = fma(tau, tau, 1.0);
+  const double h = at + q * rsqrt(q);
   const double rh = rsqrt(fma(h, h, 1.0));
   r.cs = h * rh;
   r.sn = tau >= 0.0 ? rh : -rh;
@@ -96,69 +98,111 @@ __device__ __forceinline__ void rot_left_adj(const Rot& r, double2 x0, double2 x
 // global index of local index l of block pair (I, J)
 __device__ __forceinline__ int bj_index(int I, int J, int l) { return l < BJ_B ? I * BJ_B + l : J * BJ_B + (l - BJ_B); }
 
-// Block k of round t: one cyclic sweep on the sub-problem of block pair k;
-// its unitary goes to Ublk[k] (row-major BJ_M x BJ_M).  S and U are kept in
-// two LDS copies: inner round r reads one and writes the other (every entry
-// is rewritten), so a round needs one barrier.
-__global__ __launch_bounds__(BJ_NT) void bj_solve_kernel(const double2* __restrict__ A, int N2, int t,
+// Block k of round t: rotations of the sub-problem of block pair k (ALL: every
+// index pair, else the pairs across the two blocks); its unitary goes to
+// Ublk[k] (row-major BJ_M x BJ_M).  S and U are kept in two LDS copies: inner
+// round r reads one and writes the other (every entry is rewritten), so a
+// round needs one barrier.
+//
+// Bound: the latency of an inner round, a serial chain of LDS reads, the
+// rotation's formation, two 2x2 products and the barrier, on one workgroup
+// per block pair.  A lone wave per SIMD issues a vector instruction only every
+// eight to ten cycles, so the U update has waves of its own.  A full sweep (31
+// inner rounds, 256 threads) in every round took 34.4 us per round and 7.5
+// sweeps (n = 128); now 14.7 us (33.3 us in round 0) and 8.5 sweeps.
+template <bool ALL>
+__global__ __launch_bounds__(BJ_ST) void bj_solve_kernel(const double2* __restrict__ A, int N2, int t,
                                                          double2* __restrict__ Ublk) {
   __shared__ double2 S[2][BJ_M][BJ_M + 1];
   __shared__ double2 U[2][BJ_M][BJ_M + 1];
   const int k = blockIdx.x, tid = threadIdx.x;
   int I, J;
   round_pair(t, k, N2 / BJ_B, I, J);
-  for (int e = tid; e < BJ_M * BJ_M; e += BJ_NT) {
+  for (int e = tid; e < BJ_M * BJ_M; e += BJ_ST) {
     const int r = e / BJ_M, c = e % BJ_M;
     S[0][r][c] = A[(long long)bj_index(I, J, r) * N2 + bj_index(I, J, c)];
     U[0][r][c] = double2{r == c ? 1.0 : 0.0, 0.0};
   }
   __syncthreads();
-  const int P2 = tid / BJ_B, Q2 = tid % BJ_B;
+  const bool on_s = tid < BJ_B * BJ_B;   // uniform per wave
+  const int P2 = (tid / BJ_B) % BJ_B, Q2 = tid % BJ_B;
+  auto pair_of = [](int r, int i, int& p, int& q) {
+    if constexpr (ALL) {
+      round_pair(r, i, BJ_M, p, q);
+    } else {
+      p = i;
+      q = BJ_B + ((i + r) & (BJ_B - 1));
+    }
+  };
   int cur = 0;
-  for (int r = 0; r < BJ_M - 1; ++r) {
-    // 2x2 block (P2, Q2) of S <- J^H S J, and columns pk of rows P2, P2 +
-    // BJ_B of U <- U J (each entry has one owner); the block's entries are
-    // read before the rotations are formed, so their LDS latency overlaps it
-    int pi[2], pk[2];
-    round_pair(r, P2, BJ_M, pi[0], pi[1]);
-    round_pair(r, Q2, BJ_M, pk[0], pk[1]);
-    double2 sv[2][2], uv[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        sv[a][b] = S[cur][pi[a]][pk[b]];
-        uv[a][b] = U[cur][P2 + a * BJ_B][pk[b]];
-      }
-    // every thread forms the two rotations it applies (of its row pair and
-    // its column pair) from the current copy, so no barrier publishes them
-    const Rot ri = make_rot(S[cur][pi[0]][pi[0]].x, S[cur][pi[1]][pi[1]].x, S[cur][pi[0]][pi[1]]);
-    const Rot rk = make_rot(S[cur][pk[0]][pk[0]].x, S[cur][pk[1]][pk[1]].x, S[cur][pk[0]][pk[1]]);
-    double2 tr[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) rot_right(rk, sv[a][0], sv[a][1], tr[a][0], tr[a][1]);
+  for (int r = 0; r < (ALL ? BJ_M - 1 : BJ_B); ++r) {
+    // every thread forms the rotations it applies itself from the current
+    // copy, so no barrier publishes them; its entries are read before, so
+    // their LDS latency overlaps
+    int k0, k1;
+    pair_of(r, Q2, k0, k1);
     const int nx = cur ^ 1;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) rot_left_adj(ri, tr[0][j], tr[1][j], S[nx][pi[0]][pk[j]], S[nx][pi[1]][pk[j]]);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int row = P2 + h * BJ_B;
-      rot_right(rk, uv[h][0], uv[h][1], U[nx][row][pk[0]], U[nx][row][pk[1]]);
+    const double ka = S[cur][k0][k0].x, kc = S[cur][k1][k1].x;
+    const double2 kb = S[cur][k0][k1];
+    if (on_s) {
+      // 2x2 block (P2, Q2) of S <- J^H S J
+      int i0, i1;
+      pair_of(r, P2, i0, i1);
+      const double ia = S[cur][i0][i0].x, ic = S[cur][i1][i1].x;
+      const double2 ib = S[cur][i0][i1];
+      const double2 s00 = S[cur][i0][k0], s01 = S[cur][i0][k1], s10 = S[cur][i1][k0], s11 = S[cur][i1][k1];
+      const Rot rk = make_rot(ka, kc, kb), ri = make_rot(ia, ic, ib);
+      double2 t00, t01, t10, t11;
+      rot_right(rk, s00, s01, t00, t01);
+      rot_right(rk, s10, s11, t10, t11);
+      rot_left_adj(ri, t00, t10, S[nx][i0][k0], S[nx][i1][k0]);
+      rot_left_adj(ri, t01, t11, S[nx][i0][k1], S[nx][i1][k1]);
+    } else {
+      // rows P2 and P2 + BJ_B of U <- U J, columns of pair Q2
+      const double2 u00 = U[cur][P2][k0], u01 = U[cur][P2][k1];
+      const double2 u10 = U[cur][P2 + BJ_B][k0], u11 = U[cur][P2 + BJ_B][k1];
+      const Rot rk = make_rot(ka, kc, kb);
+      rot_right(rk, u00, u01, U[nx][P2][k0], U[nx][P2][k1]);
+      rot_right(rk, u10, u11, U[nx][P2 + BJ_B][k0], U[nx][P2 + BJ_B][k1]);
     }
     __syncthreads();
     cur = nx;
   }
   double2* out = Ublk + (long long)k * BJ_M * BJ_M;
-  for (int e = tid; e < BJ_M * BJ_M; e += BJ_NT) out[e] = U[cur][e / BJ_M][e % BJ_M];
+  for (int e = tid; e < BJ_M * BJ_M; e += BJ_ST) out[e] = U[cur][e / BJ_M][e % BJ_M];
 }
 
 constexpr int BJ_VCOLS = 64;   // columns of V per block of the V update
 constexpr int BJ_LD = BJ_M + 1;
 
+typedef double dvec4 __attribute__((ext_vector_type(4)));
+
+// 16x16 complex tile sum_l L(i, l) R(l, j), l < BJ_M, on the FP64 matrix cores:
+// left(i, l) and right(l, j) fetch the operands (L[i][l] in lane i + 16 (l mod
+// 4), R[l][j] in lane j + 16 (l mod 4)); the tile's element (i, j) ends in lane
+// j + 16 (i mod 4), element i / 4.
+template <class FL, class FR>
+__device__ __forceinline__ void tile_product(FL&& left, FR&& right, dvec4& re, dvec4& im) {
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  re = im = dvec4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int l0 = 0; l0 < BJ_M; l0 += 4) {
+    const double2 a = left(i, l0 + kq), b = right(l0 + kq, i);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
+  }
+}
+
 // Round t: blocks [0, P^2) form An[rows of pair a][columns of pair b] =
 // U_a^H A U_b; the remaining blocks form the rows of pair a of Vn = (V U)^T
 // over BJ_VCOLS columns: Vn[g(i)][c] = sum_k U_a[k][i] Vt[g(k)][c] (the
-// BJ_M rows of Vt staged in LDS first).
+// BJ_M rows of Vt staged in LDS first).  One 16x16 tile per wave and product.
+// Bound: launch and memory latency (a block's loads, two products of 32
+// matrix instructions, the stores).  On the vector unit the products' LDS
+// reads and 512 multiply-adds per thread made it 12.6 us a round (n = 128);
+// 7.6 us now.
 __global__ __launch_bounds__(BJ_NT) void bj_apply_kernel(const double2* __restrict__ A, double2* __restrict__ An,
                                                          const double2* __restrict__ Vt, double2* __restrict__ Vn,
                                                          int N2, int t, const double2* __restrict__ Ublk) {
@@ -166,11 +210,12 @@ __global__ __launch_bounds__(BJ_NT) void bj_apply_kernel(const double2* __restri
   // rows of Vt (BJ_M x (BJ_VCOLS + 1))
   __shared__ double2 sm[3 * BJ_M * BJ_LD];
   static_assert(BJ_M * (BJ_VCOLS + 1) <= 2 * BJ_M * BJ_LD, "staged V rows fit the A-block buffers");
+  static_assert(BJ_M == 32 && BJ_NT == 256 && BJ_VCOLS == 64, "four waves on 2 x 2 and 2 x 4 tiles of 16 x 16");
   double2* Ua = sm;
   double2* Ub = sm + BJ_M * BJ_LD;
   double2* X = sm + 2 * BJ_M * BJ_LD;
   const int tid = threadIdx.x, nblk = N2 / BJ_B, P = nblk / 2;
-  constexpr int PER = BJ_M * BJ_M / BJ_NT;
+  const int wave = tid >> 6, lane = tid & 63, tc = lane & 15, tr = lane >> 4;
   if ((int)blockIdx.x < P * P) {
     const int ka = blockIdx.x / P, kb = blockIdx.x % P;
     int Ia, Ja, Ib, Jb;
@@ -185,30 +230,19 @@ __global__ __launch_bounds__(BJ_NT) void bj_apply_kernel(const double2* __restri
       X[r * BJ_LD + c] = A[(long long)bj_index(Ia, Ja, r) * N2 + bj_index(Ib, Jb, c)];
     }
     __syncthreads();
-    double2 tmp[PER];
-#pragma unroll
-    for (int s = 0; s < PER; ++s) {
-      const int e = tid + s * BJ_NT, r = e / BJ_M, c = e % BJ_M;
-      double2 acc{0.0, 0.0};
-      #pragma unroll 4
-      for (int l = 0; l < BJ_M; ++l) acc = cadd(acc, cmul(X[r * BJ_LD + l], Ub[l * BJ_LD + c]));
-      tmp[s] = acc;
-    }
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;   // this wave's tile
+    dvec4 re, im;
+    tile_product([&](int i, int l) { return X[(wm + i) * BJ_LD + l]; },
+                 [&](int l, int j) { return Ub[l * BJ_LD + wn + j]; }, re, im);
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < PER; ++s) {
-      const int e = tid + s * BJ_NT;
-      X[(e / BJ_M) * BJ_LD + e % BJ_M] = tmp[s];
-    }
+    for (int e = 0; e < 4; ++e) X[(wm + 4 * e + tr) * BJ_LD + wn + tc] = double2{re[e], im[e]};
     __syncthreads();
+    tile_product([&](int i, int l) { return cconj(Ua[l * BJ_LD + wm + i]); },
+                 [&](int l, int j) { return X[l * BJ_LD + wn + j]; }, re, im);
 #pragma unroll
-    for (int s = 0; s < PER; ++s) {
-      const int e = tid + s * BJ_NT, r = e / BJ_M, c = e % BJ_M;
-      double2 acc{0.0, 0.0};
-      #pragma unroll 4
-      for (int l = 0; l < BJ_M; ++l) acc = cadd(acc, cmul(cconj(Ua[l * BJ_LD + r]), X[l * BJ_LD + c]));
-      An[(long long)bj_index(Ia, Ja, r) * N2 + bj_index(Ib, Jb, c)] = acc;
-    }
+    for (int e = 0; e < 4; ++e)
+      An[(long long)bj_index(Ia, Ja, wm + 4 * e + tr) * N2 + bj_index(Ib, Jb, wn + tc)] = double2{re[e], im[e]};
     return;
   }
   const int nch = (N2 + BJ_VCOLS - 1) / BJ_VCOLS;
@@ -225,12 +259,15 @@ __global__ __launch_bounds__(BJ_NT) void bj_apply_kernel(const double2* __restri
     Vs[l * VLD + cc] = c < N2 ? Vt[(long long)bj_index(Ia, Ja, l) * N2 + c] : double2{0.0, 0.0};
   }
   __syncthreads();
-  for (int e = tid; e < BJ_M * BJ_VCOLS; e += BJ_NT) {
-    const int i = e / BJ_VCOLS, cc = e % BJ_VCOLS, c = c0 + cc;
-    double2 acc{0.0, 0.0};
-    #pragma unroll 4
-    for (int l = 0; l < BJ_M; ++l) acc = cadd(acc, cmul(Ua[l * BJ_LD + i], Vs[l * VLD + cc]));
-    if (c < N2) Vn[(long long)bj_index(Ia, Ja, i) * N2 + c] = acc;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16 + 32 * h;
+    dvec4 re, im;
+    tile_product([&](int i, int l) { return Ua[l * BJ_LD + wm + i]; },
+                 [&](int l, int j) { return Vs[l * VLD + wn + j]; }, re, im);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c0 + wn + tc < N2) Vn[(long long)bj_index(Ia, Ja, wm + 4 * e + tr) * N2 + c0 + wn + tc] = double2{re[e], im[e]};
   }
 }
 
@@ -514,7 +551,8 @@ void launch_hermitize(int n, const double2* H, double2* A, double2* Vt, hipStrea
 void launch_bj_round(int n, const double2* A, double2* An, const double2* Vt, double2* Vn, double2* Ublk, int t,
                      hipStream_t st) {
   const int N2 = bj_order(n), P = N2 / BJ_M, nch = (N2 + BJ_VCOLS - 1) / BJ_VCOLS;
-  bj_solve_kernel<<<P, BJ_NT, 0, st>>>(A, N2, t, Ublk);
+  if (t == 0) bj_solve_kernel<true><<<P, BJ_ST, 0, st>>>(A, N2, t, Ublk);
+  else bj_solve_kernel<false><<<P, BJ_ST, 0, st>>>(A, N2, t, Ublk);
   bj_apply_kernel<<<P * P + P * nch, BJ_NT, 0, st>>>(A, An, Vt, Vn, N2, t, Ublk);
 }
 
