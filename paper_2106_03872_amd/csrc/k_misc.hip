@@ -81,7 +81,7 @@ __global__ __launch_bounds__(NT) void unpack_kernel(const T* __restrict__ pk, in
 }
 
 // KB projections: P_Ip = sum over the (tile, atom) slots of atom I in
-// ascending order, DP = scale d_Ip P_Ip (Eq. vnl; scale is the analysis
+// ascending tile order, DP = scale d_Ip P_Ip (Eq. vnl; scale is the analysis
 // normalisation that the x-analysis leaves out).  One wavefront per (atom,
 // orbital): lane = 8 * slot-lane + q; slot-lanes are combined in a fixed order.
 // BATCH: block (I, y) reduces orbital rows[y].y of job rows[y].x (its
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(64) void proj_reduce_kernel(const C* __restrict__ p
   double sx = 0.0, sy = 0.0;
   if (q < np) {
     for (int k = pt.atom_slot_off[I] + sl; k < pt.atom_slot_off[I + 1]; k += 8) {
-      const C v = partial[((long long)o * pt.nslots + pt.atom_slots[k]) * np + q];
+      const C v = partial[((long long)o * pt.nslots + k) * np + q];
       sx += double(v.x);
       sy += double(v.y);
     }

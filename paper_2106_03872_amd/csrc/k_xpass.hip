@@ -132,7 +132,7 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
   // (the host plans XT projection lanes per tile)
   const int np = pt.nproj;
   const int ka = item.x, kb = item.y;
-  const int sl = item.z / np, kq = item.z - sl * np;
+  const int kq = item.z % np;
   const int glanes = 1 << (item.w & 0xff);
   const bool writer = (item.w & 256) != 0;
   // The first KP points of the item (LDS position, beta) are the same for
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
     cpos[c] = in ? cpos[c] : N0;
     cbeta[c] = in ? cbeta[c] : 0.0;
   }
-  C* pout = partial + (long long)(sA + sl) * np + kq;
+  C* pout = partial + item.z;
   const long long pstride = (long long)pt.nslots * np;
   for (int o = oa; o < ob; ++o) {
     auto next = [&] {
@@ -340,13 +340,18 @@ __device__ __forceinline__ void kb_scatter_any(C* X, const double2* dps, const P
   }
 }
 
+// SUMS: the block sums its atoms' projections itself from xproj's partial sums
+// (the same sums in the same order as proj_reduce), which saves that launch
+// where launches, not their work, bound the pass.
+//
 // BATCH: as xproj_kernel (T, U, V, d P, projector tables and orbital count
 // from the block's job).
-template <int N0, class SH, typename R, bool HB, bool BATCH = false>
+template <int N0, class SH, typename R, bool HB, bool SUMS, bool BATCH = false>
 __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restrict__ Tin, int nb,
                                                     cplx<R>* __restrict__ Uout, const double* __restrict__ V,
-                                                    const double2* __restrict__ DP, SphereTab tab, ProjTab pt,
-                                                    const cplx<R>* __restrict__ tw0, double sc_v,
+                                                    const double2* __restrict__ DP,
+                                                    const cplx<R>* __restrict__ partial, double sc_p, SphereTab tab,
+                                                    ProjTab pt, const cplx<R>* __restrict__ tw0, double sc_v,
                                                     const BatchJob* __restrict__ jobs = nullptr,
                                                     const int4* __restrict__ rows = nullptr) {
   using C = cplx<R>;
@@ -364,6 +369,7 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
     Uout = static_cast<C*>(jobs[r.x].U);
     V = jobs[r.x].V;
     DP = jobs[r.x].DP;
+    partial = static_cast<const C*>(jobs[r.x].partial);
     pt = jobs[r.x].pt;
     nb = jobs[r.x].nb;
     group_range(nb, r.y, r.z, oa, ob);
@@ -391,22 +397,58 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
   const int ndp = ns * np;   // <= KB_TILE_DP <= XT
   const long long dp_stride = (long long)pt.natoms * np;
   long long dp_off = 0;
+  int4 sd = make_int4(0, 0, 0, 0);   // SUMS: this thread's range of partial sums
+  double dd = 0.0;
+  const C* psum = nullptr;
   if (tid < ndp) {
     const int sl = tid / np, q = tid - sl * np;
-    dp_off = (long long)pt.slot_atom[sA + sl] * np + q;
+    sd = pt.slot_desc[sA + sl];
+    dp_off = (long long)sd.z * np + q;
+    if constexpr (SUMS) {
+      dd = pt.d[dp_off] * sc_p;
+      psum = partial + q;
+    }
   }
+  // d P of this thread's pair for orbital o: its partial sums in eight strided
+  // sums, added in order
+  auto sum_projection = [&](int o) {
+    double sx[8], sy[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sx[j] = sy[j] = 0.0;
+    const C* po = psum + (long long)o * pt.nslots * np;
+    for (int k0 = sd.x; k0 < sd.y; k0 += 8) {
+      C v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = k0 + j < sd.y ? po[(long long)(k0 + j) * np] : czero<C>();
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        sx[j] += double(v[j].x);
+        sy[j] += double(v[j].y);
+      }
+    }
+    double tx = 0.0, ty = 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      tx += sx[j];
+      ty += sy[j];
+    }
+    return double2{dd * tx, dd * ty};
+  };
   const int uA = pt.up_off[tile], uB = pt.up_off[tile + 1];
   stage_twiddles<N0, XT, SH::V>(tw, tw0);
   double2 dnext = {0.0, 0.0};
-  if (tid < ndp && oa < ob) dnext = DP[oa * dp_stride + dp_off];
+  if (!SUMS && tid < ndp && oa < ob) dnext = DP[oa * dp_stride + dp_off];
   for (int o = oa; o < ob; ++o) {
     // this orbital's d*P (fetched one orbital ahead); the previous orbital's
     // scatter has finished reading dps, and the stage barriers publish it
-    if (tid < ndp) dps[tid] = dnext;
+    if (tid < ndp) {
+      if constexpr (SUMS) dnext = sum_projection(o);
+      dps[tid] = dnext;
+    }
     auto next = [&] {
       if (o + 1 < ob) {
         load_inputs(pre, pos, Tin + (o + 1) * tstride, tbytes);
-        if (tid < ndp) dnext = DP[(o + 1) * dp_stride + dp_off];
+        if (!SUMS && tid < ndp) dnext = DP[(o + 1) * dp_stride + dp_off];
       }
     };
     // synthesis, then psi <- V psi as the outputs are written
@@ -610,28 +652,50 @@ bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, cons
   }
 }
 
-template <int N0, bool HB>
-static void xapply_n(const ks_system* s, int nb, const void* T, const double2* DP, void* U, hipStream_t st) {
+// Whether the x-apply blocks sum the projections themselves: every slot of a
+// tile then re-reads all partial sums of its atom (`values` in all: orbitals x
+// nproj x the sum over slots of their atom's slot count), at the head of each
+// orbital, against one launch of proj_reduce.  Up to 6 MB the launch costs more:
+// 24^3 / 10 orbitals, 47 KB: xapply 6.3 -> 6.8 us, without a launch of 2.7 us;
+// 48x40^2 / 33, 4 MB: 17.0 -> 18.1 us, without 4.1 us.  Beyond, the reads do: 32^3 /
+// 262 in a batch, 7 MB: 35.8 -> 40.9 us, without 4.8 us; 60^3 / 96, 14 MB: 72 ->
+// 110 us, without 4.8 us.
+bool xapply_sums(const ks_system* s, long long values) {
+  return s->xshape < 2 && values * (long long)(mixed(s) ? sizeof(float2) : sizeof(double2)) <= (6ll << 20);
+}
+
+template <int N0, bool HB, bool SUMS>
+static void xapply_n(const ks_system* s, int nb, const void* T, const double2* DP, const void* partial, void* U,
+                     hipStream_t st) {
   // synthesis scale Omega^-1/2 and analysis scale Omega^1/2/N folded into V
-  // (the KB coefficients carry the analysis scale from proj_reduce)
-  const double sc_v = 1.0 / (double)s->N;
+  // (the KB coefficients carry the analysis scale from the projection sums)
+  const double sc_v = 1.0 / (double)s->N, sc_p = sqrt(s->omega) / (double)s->N;
   const int ng = x_groups(s, nb);
   with_shape<N0>(s, [&](auto sh) {
     using SH = decltype(sh);
+    constexpr bool S = SUMS && SH::V == 0;
     const dim3 grid(s->ntiles, ng);
     if (!mixed(s))
-      xapply_kernel<N0, SH, double, HB><<<grid, SH::XT, 0, st>>>((const double2*)T, nb, (double2*)U, s->d_v, DP,
-                                                                sphere_tab(s), proj_tab(s), s->d_tw0, sc_v);
+      xapply_kernel<N0, SH, double, HB, S><<<grid, SH::XT, 0, st>>>((const double2*)T, nb, (double2*)U, s->d_v, DP,
+                                                                   (const double2*)partial, sc_p, sphere_tab(s),
+                                                                   proj_tab(s), s->d_tw0, sc_v);
     else
-      xapply_kernel<N0, SH, float, HB><<<grid, SH::XT, 0, st>>>((const float2*)T, nb, (float2*)U, s->d_v, DP,
-                                                               sphere_tab(s), proj_tab(s), s->d_tw0f, sc_v);
+      xapply_kernel<N0, SH, float, HB, S><<<grid, SH::XT, 0, st>>>((const float2*)T, nb, (float2*)U, s->d_v, DP,
+                                                                  (const float2*)partial, sc_p, sphere_tab(s),
+                                                                  proj_tab(s), s->d_tw0f, sc_v);
   });
 }
 
-bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP, void* U, hipStream_t st) {
+bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP, const void* partial, void* U,
+                   hipStream_t st) {
   switch (s->n[0]) {
-#define KS_CASE(v) \
-  case v: s->x_half ? xapply_n<v, true>(s, nb, T, DP, U, st) : xapply_n<v, false>(s, nb, T, DP, U, st); return true;
+#define KS_CASE(v)                                                                                         \
+  case v:                                                                                                  \
+    if (partial) s->x_half ? xapply_n<v, true, true>(s, nb, T, DP, partial, U, st)                         \
+                           : xapply_n<v, false, true>(s, nb, T, DP, partial, U, st);                       \
+    else s->x_half ? xapply_n<v, true, false>(s, nb, T, DP, partial, U, st)                                \
+                   : xapply_n<v, false, false>(s, nb, T, DP, partial, U, st);                              \
+    return true;
     KS_SIZES(KS_CASE)
 #undef KS_CASE
     default:
@@ -642,13 +706,14 @@ bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP,
 // Batched launches: one x-pass launch over several systems of the grid (all
 // of one tile shape, that of s).
 template <int N0, bool HB>
-static void x_batch_n(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool apply,
+static void x_batch_n(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool apply, bool sums,
                       hipStream_t st) {
   const dim3 grid(s->ntiles, nrows);
   const double scale = s->dV / sqrt(s->omega);
-  const double sc_v = 1.0 / (double)s->N;
+  const double sc_v = 1.0 / (double)s->N, sc_p = sqrt(s->omega) / (double)s->N;
   with_shape<N0>(s, [&](auto sh) {
     using SH = decltype(sh);
+    constexpr bool S = SH::V == 0;
     if (!apply) {
       if (!mixed(s))
         xproj_kernel<N0, SH, double, HB, false, true><<<grid, SH::XT, 0, st>>>(
@@ -657,21 +722,23 @@ static void x_batch_n(const ks_system* s, const BatchJob* jobs, const int4* rows
         xproj_kernel<N0, SH, float, HB, false, true><<<grid, SH::XT, 0, st>>>(
             nullptr, 0, nullptr, sphere_tab(s), ProjTab{}, s->d_tw0f, scale, nullptr, nullptr, 0.0, jobs, rows);
     } else if (!mixed(s)) {
-      xapply_kernel<N0, SH, double, HB, true><<<grid, SH::XT, 0, st>>>(
-          nullptr, 0, nullptr, nullptr, nullptr, sphere_tab(s), ProjTab{}, s->d_tw0, sc_v, jobs, rows);
+      auto* k = sums ? xapply_kernel<N0, SH, double, HB, S, true> : xapply_kernel<N0, SH, double, HB, false, true>;
+      k<<<grid, SH::XT, 0, st>>>(nullptr, 0, nullptr, nullptr, nullptr, nullptr, sc_p, sphere_tab(s), ProjTab{},
+                                 s->d_tw0, sc_v, jobs, rows);
     } else {
-      xapply_kernel<N0, SH, float, HB, true><<<grid, SH::XT, 0, st>>>(
-          nullptr, 0, nullptr, nullptr, nullptr, sphere_tab(s), ProjTab{}, s->d_tw0f, sc_v, jobs, rows);
+      auto* k = sums ? xapply_kernel<N0, SH, float, HB, S, true> : xapply_kernel<N0, SH, float, HB, false, true>;
+      k<<<grid, SH::XT, 0, st>>>(nullptr, 0, nullptr, nullptr, nullptr, nullptr, sc_p, sphere_tab(s), ProjTab{},
+                                 s->d_tw0f, sc_v, jobs, rows);
     }
   });
 }
 
-bool launch_x_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool apply,
+bool launch_x_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool apply, bool sums,
                     hipStream_t st) {
   switch (s->n[0]) {
 #define KS_CASE(v) \
-  case v: s->x_half ? x_batch_n<v, true>(s, jobs, rows, nrows, apply, st) \
-                    : x_batch_n<v, false>(s, jobs, rows, nrows, apply, st); return true;
+  case v: s->x_half ? x_batch_n<v, true>(s, jobs, rows, nrows, apply, sums, st) \
+                    : x_batch_n<v, false>(s, jobs, rows, nrows, apply, sums, st); return true;
     KS_SIZES(KS_CASE)
 #undef KS_CASE
     default:

@@ -276,7 +276,7 @@ struct ProjHost {
   int nproj = 1, npoints = 0, nruns = 0, ntiles = 0, xnb = 32, lanes = 256;
   std::vector<double> brows;
   std::vector<int> brow_input;   // input row of each beta row
-  std::vector<int> pt_lds, slot_off, slot_atom, slot_pt, atom_slot_off, atom_slots;
+  std::vector<int> pt_lds, slot_off, slot_atom, slot_pt, atom_slot_off, slot_pos;
   std::vector<int> up_off, up_lds, up_ent, ent_slot, ent_brow;
   std::vector<int4> item;
 };
@@ -364,8 +364,17 @@ ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, 
   // lane's share of the slot's beta rows fits the registers cached across
   // orbitals; when a tile would need more lanes than the block has, the
   // largest groups are halved (their lanes then loop over extra rows).
-  // item = (first row, end row, local slot * nproj + projector, g | 256 for
-  // the group's first lane).
+  // item = (first row, end row, output index, g | 256 for the group's first
+  // lane).  An orbital's partial sums are ordered by atom (then tile), so an
+  // atom's sums are contiguous: output index = slot_pos * nproj + projector.
+  h.atom_slot_off.assign(natoms + 1, 0);
+  h.slot_pos.assign(nslots, 0);
+  for (int k = 0; k < nslots; ++k) h.atom_slot_off[h.slot_atom[k] + 1]++;
+  for (int I = 0; I < natoms; ++I) h.atom_slot_off[I + 1] += h.atom_slot_off[I];
+  {
+    std::vector<int> fill(h.atom_slot_off.begin(), h.atom_slot_off.end() - 1);
+    for (int k = 0; k < nslots; ++k) h.slot_pos[k] = fill[h.slot_atom[k]]++;
+  }
   h.item.assign((size_t)nt * lanes, make_int4(0, 0, 0, 0));
   for (int t = 0; t < nt; ++t) {
     const int s0 = h.slot_off[t], ns = h.slot_off[t + 1] - s0;
@@ -393,17 +402,9 @@ ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, 
       for (int q = 0; q < np; ++q, base += g)
         for (int sg = 0; sg < g; ++sg)
           h.item[(size_t)t * lanes + base + sg] =
-              make_int4(k0 + (int)((long long)len * sg / g), k0 + (int)((long long)len * (sg + 1) / g), j * np + q,
-                        lg[j] | (sg == 0 ? 256 : 0));
+              make_int4(k0 + (int)((long long)len * sg / g), k0 + (int)((long long)len * (sg + 1) / g),
+                        h.slot_pos[s0 + j] * np + q, lg[j] | (sg == 0 ? 256 : 0));
     }
-  }
-  h.atom_slot_off.assign(natoms + 1, 0);
-  h.atom_slots.assign(nslots, 0);
-  for (int k = 0; k < nslots; ++k) h.atom_slot_off[h.slot_atom[k] + 1]++;
-  for (int I = 0; I < natoms; ++I) h.atom_slot_off[I + 1] += h.atom_slot_off[I];
-  {
-    std::vector<int> fill(h.atom_slot_off.begin(), h.atom_slot_off.end() - 1);
-    for (int k = 0; k < nslots; ++k) h.atom_slots[fill[h.slot_atom[k]]++] = k;
   }
   // scatter side: order (tile, pencil, j0, atom); one entry per (point, atom)
   std::vector<int> order(pts.size());
@@ -535,16 +536,21 @@ ks_status hpsi_packed(ks_system* s, int nb, const void* win, bool win_fp64, void
                       void* acc2 = nullptr) {
   ks_status r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, win, win_fp64, s->T, st); });
   if (r != KS_OK) return r;
+  const void* sums = nullptr;   // partial sums that the x-apply pass adds itself
   if (s->natoms > 0 && s->proj_mode == 1 && !rho) {
     r = kcall(s, KS_K_GPROJ, st, "gproj", [&] { return launch_gproj(s, nb, win, win_fp64, s->DP, st); });
     if (r != KS_OK) return r;
   } else if (s->natoms > 0) {
     r = kcall(s, KS_K_XPROJ, st, "xproj", [&] { return launch_xproj(s, nb, s->T, s->partial, occ, rho, accumulate, st); });
     if (r != KS_OK) return r;
-    r = kcall(s, KS_K_PROJ_REDUCE, st, "proj_reduce", [&] { return launch_proj_reduce(s, nb, s->partial, s->DP, st); });
-    if (r != KS_OK) return r;
+    if (xapply_sums(s, s->slot_sq * s->nproj * nb)) {
+      sums = s->partial;
+    } else {
+      r = kcall(s, KS_K_PROJ_REDUCE, st, "proj_reduce", [&] { return launch_proj_reduce(s, nb, s->partial, s->DP, st); });
+      if (r != KS_OK) return r;
+    }
   }
-  r = kcall(s, KS_K_XAPPLY, st, "xapply", [&] { return launch_xapply(s, nb, s->T, s->DP, s->U, st); });
+  r = kcall(s, KS_K_XAPPLY, st, "xapply", [&] { return launch_xapply(s, nb, s->T, s->DP, sums, s->U, st); });
   if (r != KS_OK) return r;
   return kcall(s, KS_K_PLANE_FWD, st, "plane_fwd",
                [&] { return launch_plane_fwd(s, nb, s->U, win, win_fp64, wout, acc, acc2, mode, tay, st); });
@@ -1043,8 +1049,8 @@ void ks_system_destroy(ks_system* s) {
   free_workspace(s);
   free_gtab(s, s->gp);
   void* ptrs[] = {s->d_plane_col0, s->d_plane_m1lo, s->d_col_off, s->d_col_m2lo, s->d_tw0, s->d_tw1,
-                  s->d_tw0f, s->d_tw1f, s->d_v, s->d_vloc, s->d_kin, s->d_hbox, s->d_rho_w, s->d_pt_lds, s->d_slot_off, s->d_slot_atom, s->d_slot_pt,
-                  s->d_atom_slot_off, s->d_atom_slots,
+                  s->d_tw0f, s->d_tw1f, s->d_v, s->d_vloc, s->d_kin, s->d_hbox, s->d_rho_w, s->d_pt_lds, s->d_slot_off, s->d_slot_desc, s->d_slot_pt,
+                  s->d_atom_slot_off,
                   s->d_up_off, s->d_up_key, s->d_up_x, s->d_x_slot, s->d_beta, s->d_up_beta, s->d_x_beta, s->d_item,
                   s->d_kb, s->red, s->ortho_pk, s->ortho_S, s->ortho_W, s->ortho_info, s->ortho_diag, s->gemm_part};
   for (void* p : ptrs) dfree(s, p);
@@ -1102,6 +1108,15 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
       for (int c = 0; c < np; ++c) x_beta.push_back(ph.brows[(size_t)ph.ent_brow[e] * np + c]);
     }
   }
+  // per slot: range of its atom's partial sums, atom
+  const int nslots = (int)ph.slot_atom.size();
+  std::vector<int4> slot_desc(nslots);
+  long long slot_sq = 0;
+  for (int k = 0; k < nslots; ++k) {
+    const int I = ph.slot_atom[k];
+    slot_desc[k] = make_int4(ph.atom_slot_off[I], ph.atom_slot_off[I + 1], I, 0);
+    slot_sq += ph.atom_slot_off[I + 1] - ph.atom_slot_off[I];
+  }
   // New device copies first; the system's tables are replaced only when
   // every one of them was allocated and filled, so a failure (KS_ENOMEM)
   // leaves the old tables, shape and workspace in place.
@@ -1116,9 +1131,9 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
       KS_HIP(s, hipMemcpy(*dst, vec.data(), vec.size() * sizeof(T), hipMemcpyHostToDevice));
     return KS_OK;
   };
-  int *pt_lds, *slot_off, *slot_atom, *slot_pt, *atom_slot_off, *atom_slots, *up_off, *up_key2, *up_x2, *x_slot2;
+  int *pt_lds, *slot_off, *slot_pt, *atom_slot_off, *up_off, *up_key2, *up_x2, *x_slot2;
   double *brows, *up_beta2, *x_beta2, *kb2;
-  int4* item;
+  int4 *item, *slot_desc2;
   void* partial = nullptr;
   double2* DP = nullptr;
   const int na = (natoms > 0 && ph.npoints > 0) ? natoms : 0;
@@ -1126,8 +1141,8 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
   const size_t dbytes = (size_t)s->cb * std::max(1, na) * std::max(1, np) * sizeof(double2);
   ks_status st;
   if ((st = put(ph.pt_lds, &pt_lds)) != KS_OK || (st = put(ph.slot_off, &slot_off)) != KS_OK ||
-      (st = put(ph.slot_atom, &slot_atom)) != KS_OK || (st = put(ph.slot_pt, &slot_pt)) != KS_OK ||
-      (st = put(ph.atom_slot_off, &atom_slot_off)) != KS_OK || (st = put(ph.atom_slots, &atom_slots)) != KS_OK ||
+      (st = put(slot_desc, &slot_desc2)) != KS_OK || (st = put(ph.slot_pt, &slot_pt)) != KS_OK ||
+      (st = put(ph.atom_slot_off, &atom_slot_off)) != KS_OK ||
       (st = put(ph.up_off, &up_off)) != KS_OK || (st = put(up_key, &up_key2)) != KS_OK ||
       (st = put(up_x, &up_x2)) != KS_OK || (st = put(x_slot, &x_slot2)) != KS_OK ||
       (st = put(ph.brows, &brows)) != KS_OK || (st = put(up_beta, &up_beta2)) != KS_OK ||
@@ -1144,10 +1159,9 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
   };
   swap_in(s->d_pt_lds, pt_lds);
   swap_in(s->d_slot_off, slot_off);
-  swap_in(s->d_slot_atom, slot_atom);
+  swap_in(s->d_slot_desc, slot_desc2);
   swap_in(s->d_slot_pt, slot_pt);
   swap_in(s->d_atom_slot_off, atom_slot_off);
-  swap_in(s->d_atom_slots, atom_slots);
   swap_in(s->d_up_off, up_off);
   swap_in(s->d_up_key, up_key2);
   swap_in(s->d_up_x, up_x2);
@@ -1163,7 +1177,8 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
   s->dp_cap = dbytes;
   s->natoms = na;
   s->nproj = np;
-  s->nslots = (int)ph.slot_atom.size();
+  s->nslots = nslots;
+  s->slot_sq = slot_sq;
   s->nruns = ph.nruns;
   s->npoints = ph.npoints;
   s->nuniq = (int)ph.up_lds.size();
@@ -1914,13 +1929,14 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
     std::vector<BatchJob> jobs;
     std::vector<int4> rx, rp, rr;
     int njobs = 0, max_natoms = 0;
+    bool sums = false;
   };
   std::vector<Host> hp(npass);
   size_t total_bytes = 0;
   for (int p = 0; p < npass; ++p) {
     Host& h = hp[p];
     std::vector<int> js, nbs, o0s;
-    long long total = 0;
+    long long total = 0, sq = 0;
     for (int j = 0; j < nstates; ++j) {
       const ks_state* t = states[j];
       const int cl = chunk_len(t->sys, t->norb), o0 = p * cl;
@@ -1929,9 +1945,11 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
       o0s.push_back(o0);
       nbs.push_back(std::min(cl, t->norb - o0));
       total += nbs.back();
+      sq += t->sys->slot_sq * t->sys->nproj * nbs.back();
       h.max_natoms = std::max(h.max_natoms, t->sys->natoms);
     }
     h.njobs = (int)js.size();
+    h.sums = xapply_sums(s0, sq);
     const int gx = x_group_size(s0, total), gp = plane_group_size(s0, total);
     for (int q = 0; q < h.njobs; ++q) {
       const int nb = nbs[q];
@@ -2002,6 +2020,7 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
     bp.nrows_p = (int)h.rp.size();
     bp.nrows_r = (int)h.rr.size();
     bp.max_natoms = h.max_natoms;
+    bp.sums = h.sums;
   }
   const hipError_t e = hipMemcpy(b->dev, host.data(), b->dev_bytes, hipMemcpyHostToDevice);
   if (e != hipSuccess) {
@@ -2073,11 +2092,11 @@ static ks_status batch_taylor(ks_batch* b, double dt, int nsteps, hipStream_t st
           if ((r = kcall(s0, KS_K_XPROJ, st, "xproj",
                          [&] {
                            return row_slices(bp.rows_x, bp.nrows_x, [&](const int4* rs, int n) {
-                             return launch_x_batch(s0, jobs, rs, n, false, st);
+                             return launch_x_batch(s0, jobs, rs, n, false, false, st);
                            });
                          })) != KS_OK)
             return r;
-          if ((r = kcall(s0, KS_K_PROJ_REDUCE, st, "proj_reduce", [&] {
+          if (!bp.sums && (r = kcall(s0, KS_K_PROJ_REDUCE, st, "proj_reduce", [&] {
                  return row_slices(bp.rows_r, bp.nrows_r, [&](const int4* rs, int n) {
                    return launch_proj_reduce_batch(s0, jobs, rs, n, bp.max_natoms, st);
                  });
@@ -2087,7 +2106,7 @@ static ks_status batch_taylor(ks_batch* b, double dt, int nsteps, hipStream_t st
         if ((r = kcall(s0, KS_K_XAPPLY, st, "xapply",
                        [&] {
                          return row_slices(bp.rows_x, bp.nrows_x, [&](const int4* rs, int n) {
-                           return launch_x_batch(s0, jobs, rs, n, true, st);
+                           return launch_x_batch(s0, jobs, rs, n, true, bp.sums, st);
                          });
                        })) != KS_OK)
           return r;

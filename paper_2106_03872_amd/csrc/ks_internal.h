@@ -37,10 +37,9 @@ struct SphereTab {
 struct ProjTab {
   const int* pt_lds;         // [npoints] LDS offset of each beta row's point
   const int* slot_off;       // [ntiles+1] slot range of each tile
-  const int* slot_atom;      // [nslots]
+  const int4* slot_desc;     // [nslots] first and end partial sum of the slot's atom (atom order), atom
   const int* slot_pt;        // [nslots+1] beta-row range of each slot
-  const int* atom_slot_off;  // [natoms+1]
-  const int* atom_slots;     // slots of each atom, ascending
+  const int* atom_slot_off;  // [natoms+1] partial sums of each atom (partials are ordered by atom, then tile)
   const int* up_off;         // [ntiles+1] unique-point range of each tile
   const int* up_key;         // [nunique] LDS offset | primary slot << 16 | extra entries << 24
   const int* up_x;           // [nunique] first extra entry of the point
@@ -165,11 +164,12 @@ struct ks_system {
   // (real space), 1 = the reciprocal-space split-BF16 product with the table
   // gp (mixed precision; ks_tuning.projection)
   int proj_mode = 0;
-  int *d_pt_lds = nullptr, *d_slot_off = nullptr, *d_slot_atom = nullptr, *d_slot_pt = nullptr,
-      *d_atom_slot_off = nullptr, *d_atom_slots = nullptr, *d_up_off = nullptr, *d_up_key = nullptr,
+  int *d_pt_lds = nullptr, *d_slot_off = nullptr, *d_slot_pt = nullptr,
+      *d_atom_slot_off = nullptr, *d_up_off = nullptr, *d_up_key = nullptr,
       *d_up_x = nullptr, *d_x_slot = nullptr;
   double *d_beta = nullptr, *d_up_beta = nullptr, *d_x_beta = nullptr, *d_kb = nullptr;
-  int4* d_item = nullptr;
+  int4 *d_item = nullptr, *d_slot_desc = nullptr;
+  long long slot_sq = 0;   // sum over slots of their atom's slot count
   ks::GTab gp;
   // the projector inputs as last set, kept so the per-tile tables can be
   // rebuilt for another tile shape
@@ -252,6 +252,7 @@ struct ks_batch_pass {
   int4* rows_p = nullptr;                 // plane-pass rows
   int4* rows_r = nullptr;                 // projection-reduce rows (job, orbital)
   int nrows_x = 0, nrows_p = 0, nrows_r = 0, max_natoms = 0;
+  bool sums = false;                      // projections summed in the x-apply pass (no proj_reduce)
 };
 
 // Several resident states of distinct systems of one grid, stepped together
@@ -280,7 +281,11 @@ bool launch_plane_inv(const ks_system* s, int nb, const void* pk, bool in_fp64, 
 bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, const double* occ, double* rho,
                   int accumulate, hipStream_t st);
 bool launch_proj_reduce(const ks_system* s, int nb, const void* partial, double2* DP, hipStream_t st);
-bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP, void* U, hipStream_t st);
+// partial: the projections are also summed here from xproj's partial sums
+// (xapply_sums says where that pays) instead of read from DP
+bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP, const void* partial, void* U,
+                   hipStream_t st);
+bool xapply_sums(const ks_system* s, long long values);
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
                       void* acc, void* acc2, HMode mode, Taylor tay, hipStream_t st);
 bool launch_xdens(const ks_system* s, int nb, const void* T, const double* occ, double* rho, int accumulate,
@@ -293,7 +298,8 @@ bool launch_xdens(const ks_system* s, int nb, const void* T, const double* occ, 
 // groups, Taylor mode with the jobs' acc and wout.
 bool launch_plane_inv_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool in_fp64,
                             hipStream_t st);
-bool launch_x_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool apply, hipStream_t st);
+bool launch_x_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool apply, bool sums,
+                    hipStream_t st);
 bool launch_proj_reduce_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, int max_natoms,
                               hipStream_t st);
 bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool win_fp64,
@@ -404,10 +410,9 @@ inline ProjTab proj_tab(const ks_system* s) {
   ProjTab c;
   c.pt_lds = s->d_pt_lds;
   c.slot_off = s->d_slot_off;
-  c.slot_atom = s->d_slot_atom;
+  c.slot_desc = s->d_slot_desc;
   c.slot_pt = s->d_slot_pt;
   c.atom_slot_off = s->d_atom_slot_off;
-  c.atom_slots = s->d_atom_slots;
   c.up_off = s->d_up_off;
   c.up_key = s->d_up_key;
   c.up_x = s->d_up_x;
