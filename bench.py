@@ -55,8 +55,8 @@ def alg_bytes(info, spec, kernel, S=16):
         return parts + info["natoms"] * info["nproj"] * S, 0
     if kernel == "xapply":
         return 2 * box_planes, N * 8 + beta
-    if kernel == "plane_fwd":       # Taylor mode: U, w_in, acc read+write, w_out for 3 of 4 powers
-        return box_planes + npw + 2 * npw + 0.75 * npw, 0
+    if kernel == "plane_fwd":       # Taylor mode: U, w_in, acc read+write, w_out for 3 of 4 powers, T of the next H psi
+        return 2 * box_planes + npw + 2 * npw + 0.75 * npw, 0
     if kernel == "xdens":
         return box_planes, 2 * N * 8
     if kernel == "pack":

@@ -113,6 +113,43 @@ __device__ __forceinline__ PlaneCols plane_cols(const SphereTab& tab, int pi, in
   return p;
 }
 
+// z-synthesis of the columns of go <= G orbitals' plane into Z, then
+// y-synthesis from Z, through Y, to T (out: this plane of the first orbital's
+// T; gstride: bytes between orbitals).  coef(g, k): packed coefficient k of
+// the plane of orbital g (it may live in Y: it is read before Y is written).
+// Ends with a block barrier.
+template <int N, int NTH, int YB, int ZB, int G, bool HB, typename C, class F>
+__device__ __forceinline__ void plane_synthesis(C* Z, C* Y, const C* tw, const int* s_off, const int* s_m2lo,
+                                                const PlaneCols& pc, int go, gbuf out, unsigned gstride, F&& coef) {
+  const int nc = pc.nc, m1lo = pc.m1lo, nz = go * nc;
+  for (int zb = 0; zb < nz; zb += ZB) {
+    auto load = [&](int t, int e) -> C {
+      int g = 0, c = zb + t;
+#pragma unroll
+      for (int i = 1; i < G; ++i) g += zb + t >= i * nc;
+      c -= g * nc;
+      const int idx = fold(e, N) - s_m2lo[c];
+      return (idx >= 0 && idx < s_off[c + 1] - s_off[c]) ? coef(g, s_off[c] + idx) : czero<C>();
+    };
+    if constexpr (HB) fft_io<N, +1, ZB, NTH, SRC_FN, DST_LDS, C>(Z + zb * (N + 1), N + 1, nz - zb, tw, banded(load), no_store{});
+    else fft_io<N, +1, ZB, NTH, SRC_FN, DST_LDS, C>(Z + zb * (N + 1), N + 1, nz - zb, tw, load, no_store{});
+  }
+  for (int y0 = 0; y0 < go * N; y0 += YB) {
+    auto load = [&](int t, int e) -> C {
+      const int y = y0 + t, g = G == 1 ? 0 : y / N, w = G == 1 ? y : y % N;
+      const int c = fold(e, N) - m1lo;
+      return (c >= 0 && c < nc) ? Z[(g * nc + c) * (N + 1) + w] : czero<C>();
+    };
+    auto store = [&](int t, int e, C v, int, int) {
+      const int y = y0 + t, g = G == 1 ? 0 : y / N, w = G == 1 ? y : y % N;
+      buf_store<true>(out, g * gstride + (unsigned)((e * N + w) * (int)sizeof(C)), v);
+    };
+    if constexpr (HB) fft_io<N, +1, YB, NTH, SRC_FN, DST_FN, C>(Y, N + 1, go * N - y0, tw, banded(load), store);
+    else fft_io<N, +1, YB, NTH, SRC_FN, DST_FN, C>(Y, N + 1, go * N - y0, tw, load, store);
+    __syncthreads();
+  }
+}
+
 // ----------------------------------------------------------- plane synthesis
 // Block (plane pi, orbital group).  G orbitals of the group at a time: their
 // packed coefficients of the plane (contiguous, so the loads coalesce; fetched
@@ -159,7 +196,7 @@ __global__ __launch_bounds__((pcfg<N, R, false>::NT)) __attribute__((amdgpu_wave
     orbital_range(nb, oa, ob);
   }
   const PlaneCols pc = plane_cols<NTH>(tab, pi, s_off, s_m2lo);
-  const int nc = pc.nc, npp = pc.npp, m1lo = pc.m1lo;
+  const int npp = pc.npp;
   // this thread's first EP coefficients of each of the next G orbitals
   TIN cin[G][EP];
   auto fetch = [&](int o) {
@@ -194,50 +231,14 @@ __global__ __launch_bounds__((pcfg<N, R, false>::NT)) __attribute__((amdgpu_wave
       if (o + G < ob) fetch(o + G);
       __syncthreads();
     }
-    const int nz = go * nc;
-    for (int zb = 0; zb < nz; zb += ZB) {
-      auto split = [&](int t, int& g, int& c) {
-        c = zb + t;
-        g = 0;
-#pragma unroll
-        for (int i = 1; i < G; ++i) g += zb + t >= i * nc;
-        c -= g * nc;
-      };
-      auto run = [&](auto load) {
-        if constexpr (HB) fft_io<N, +1, ZB, NTH, SRC_FN, DST_LDS, C>(Z + zb * (N + 1), N + 1, nz - zb, tw, banded(load), no_store{});
-        else fft_io<N, +1, ZB, NTH, SRC_FN, DST_LDS, C>(Z + zb * (N + 1), N + 1, nz - zb, tw, load, no_store{});
-      };
-      if (stage) {
-        run([&](int t, int e) -> C {
-          int g, c;
-          split(t, g, c);
-          const int idx = fold(e, N) - s_m2lo[c];
-          return (idx >= 0 && idx < s_off[c + 1] - s_off[c]) ? S[g * npp + s_off[c] + idx] : czero<C>();
-        });
-      } else {
-        run([&](int t, int e) -> C {
-          int g, c;
-          split(t, g, c);
-          const int idx = fold(e, N) - s_m2lo[c];
-          const TIN* in = pk + (long long)(o + g) * pk_stride + pc.e0;
-          return (idx >= 0 && idx < s_off[c + 1] - s_off[c]) ? cvt<C>(in[s_off[c] + idx]) : czero<C>();
-        });
-      }
-    }
     const gbuf out = make_gbuf(Tout + ((long long)o * tab.nplanes + pi) * N * N, OOB);
-    for (int y0 = 0; y0 < go * N; y0 += YB) {
-      auto load = [&](int t, int e) -> C {
-        const int y = y0 + t, g = G == 1 ? 0 : y / N, w = G == 1 ? y : y % N;
-        const int c = fold(e, N) - m1lo;
-        return (c >= 0 && c < nc) ? Z[(g * nc + c) * (N + 1) + w] : czero<C>();
-      };
-      auto store = [&](int t, int e, C v, int, int) {
-        const int y = y0 + t, g = G == 1 ? 0 : y / N, w = G == 1 ? y : y % N;
-        buf_store<true>(out, g * gstride + (unsigned)((e * N + w) * (int)sizeof(C)), v);
-      };
-      if constexpr (HB) fft_io<N, +1, YB, NTH, SRC_FN, DST_FN, C>(Y, N + 1, go * N - y0, tw, banded(load), store);
-      else fft_io<N, +1, YB, NTH, SRC_FN, DST_FN, C>(Y, N + 1, go * N - y0, tw, load, store);
-      __syncthreads();
+    if (stage) {
+      plane_synthesis<N, NTH, YB, ZB, G, HB>(Z, Y, tw, s_off, s_m2lo, pc, go, out, gstride,
+                                             [&](int g, int k) { return S[g * pc.npp + k]; });
+    } else {
+      plane_synthesis<N, NTH, YB, ZB, G, HB>(Z, Y, tw, s_off, s_m2lo, pc, go, out, gstride, [&](int g, int k) {
+        return cvt<C>((pk + (long long)(o + g) * pk_stride + pc.e0)[k]);
+      });
     }
   }
 }
@@ -254,14 +255,23 @@ __global__ __launch_bounds__((pcfg<N, R, false>::NT)) __attribute__((amdgpu_wave
 // energies are found once per block.
 // LDS: twiddles [N] | Z [G ncol][N+1] | Y [YB][N+1].
 
-// BATCH: as plane_inv_kernel; U, win, wout, acc and the orbital count come
+// next: the block goes on to the plane synthesis of the next H psi: with 1 of
+// the H psi just formed (the next power of H), with 2 of the
+// accumulated state, from the coefficients in LDS into T (whose last reader,
+// the x-apply pass, is done).  Saves a launch, a read of the coefficients and
+// the start of a block (tables, twiddles): a step of 4 H psi measured 506 -> 451
+// us (24^3, 10 orbitals, mixed), 1480 -> 1435 (60^3, 96, mixed), 2585 -> 2531
+// (64^3, 128, FP64), 34.5 -> 33.7 ms (96^3, 512, FP64), 53.0 -> 51.1 ms (120^3,
+// 1024, mixed).
+//
+// BATCH: as plane_inv_kernel; U, win, wout, acc, T and the orbital count come
 // from the block's job (no second accumulator).
 template <int N, typename R, typename TW, bool HB, bool BATCH = false>
 __global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves_per_eu(pcfg<N, R, true>::W))) void plane_fwd_kernel(
     const cplx<R>* __restrict__ Uin, int nb, const TW* win, cplx<R>* __restrict__ wout, double2* acc, double2* acc2,
     int pk_stride, int acc_stride, SphereTab tab, const double* __restrict__ kin, const cplx<R>* __restrict__ twN,
-    int ncol_max, int mode, Taylor tay, const BatchJob* __restrict__ jobs = nullptr,
-    const int4* __restrict__ rows = nullptr) {
+    int ncol_max, int mode, Taylor tay, int next, cplx<R>* __restrict__ Tout,
+    const BatchJob* __restrict__ jobs = nullptr, const int4* __restrict__ rows = nullptr) {
   using C = cplx<R>;
   constexpr int NTH = pcfg<N, R, true>::NT, YB = pcfg<N, R, true>::YB, ZB = pcfg<N, R, true>::ZB, G = pcfg<N, R, true>::G;
   constexpr int EP = plane_ep(N, NTH);
@@ -280,6 +290,7 @@ __global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves
     wout = static_cast<cplx<R>*>(jobs[r.x].wout);
     acc = jobs[r.x].acc;
     acc2 = nullptr;
+    Tout = static_cast<cplx<R>*>(jobs[r.x].T);
     nb = jobs[r.x].nb;
     group_range(nb, r.y, r.z, oa, ob);
   } else {
@@ -368,6 +379,7 @@ __global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves
       const gbuf wp = make_gbuf(wout + ro, OOB);
       const gbuf ap = make_gbuf(acc + ra, OOB);
       const C* const zg = Z + g * nc * (N + 1);
+      C* const sg = Y + g * npp;   // next: staged coefficients of the synthesis
       auto epilogue = [&](int k, int zp, double K, TW w, double2 a) {
         const C ph = zg[zp];
         const double2 hw{K * double(w.x) + double(ph.x), K * double(w.y) + double(ph.y)};
@@ -378,6 +390,7 @@ __global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves
           a.x += tay.coef.x * hw.x - tay.coef.y * hw.y;
           a.y += tay.coef.x * hw.y + tay.coef.y * hw.x;
           buf_store(ap, k * (unsigned)sizeof(double2), a);
+          if (next) sg[k] = to_c<C>(next == 1 ? hw : a);
           if (acc2) {
             double2 b = (acc2 + ra)[k];
             b.x += tay.coef2.x * hw.x - tay.coef2.y * hw.y;
@@ -396,6 +409,10 @@ __global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves
                  mode != H_OUT ? (acc + ra)[k] : double2{0.0, 0.0});
     }
     __syncthreads();   // Z is rewritten by the next orbitals
+    if (next)
+      plane_synthesis<N, NTH, YB, ZB, G, HB>(Z, Y, tw, s_off, s_m2lo, pc, go,
+                                             make_gbuf(Tout + ((long long)o * tab.nplanes + pi) * N * N, OOB), gstride,
+                                             [&](int g, int k) { return Y[g * npp + k]; });
   }
 }
 
@@ -506,31 +523,33 @@ bool launch_plane_inv_batch(const ks_system* s, const BatchJob* jobs, const int4
 
 template <int N, typename R, typename TW, bool B>
 static void plane_fwd_t(const ks_system* s, int nb, const void* U, const void* win, void* wout, void* acc, void* acc2,
-                        HMode mode, Taylor tay, const void* tw, const BatchRef& b, hipStream_t st) {
+                        HMode mode, Taylor tay, int next, void* T, const void* tw, const BatchRef& b, hipStream_t st) {
   using PC = pcfg<N, R, true>;
   const dim3 grid(s->nplanes, B ? b.nrows : plane_groups(s, nb));
-  if (s->yz_half)
-    plane_fwd_kernel<N, R, TW, true, B><<<grid, PC::NT, plane_smem<true>(s), st>>>(
-        (const cplx<R>*)U, nb, (const TW*)win, (cplx<R>*)wout, (double2*)acc, (double2*)acc2, s->npw_stride, s->npw_stride,
-        sphere_tab(s), s->d_kin, (const cplx<R>*)tw, s->ncol_max, (int)mode, tay, b.jobs, b.rows);
-  else
-    plane_fwd_kernel<N, R, TW, false, B><<<grid, PC::NT, plane_smem<true>(s), st>>>(
-        (const cplx<R>*)U, nb, (const TW*)win, (cplx<R>*)wout, (double2*)acc, (double2*)acc2, s->npw_stride, s->npw_stride,
-        sphere_tab(s), s->d_kin, (const cplx<R>*)tw, s->ncol_max, (int)mode, tay, b.jobs, b.rows);
+  auto* k = s->yz_half ? plane_fwd_kernel<N, R, TW, true, B> : plane_fwd_kernel<N, R, TW, false, B>;
+  k<<<grid, PC::NT, plane_smem<true>(s), st>>>((const cplx<R>*)U, nb, (const TW*)win, (cplx<R>*)wout, (double2*)acc,
+                                               (double2*)acc2, s->npw_stride, s->npw_stride, sphere_tab(s), s->d_kin,
+                                               (const cplx<R>*)tw, s->ncol_max, (int)mode, tay, next, (cplx<R>*)T,
+                                               b.jobs, b.rows);
 }
 
 template <int N, bool B>
 static void plane_fwd_n(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
-                        void* acc, void* acc2, HMode mode, Taylor tay, const BatchRef& b, hipStream_t st) {
-  if (!mixed(s)) plane_fwd_t<N, double, double2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, s->d_tw1, b, st);
-  else if (win_fp64) plane_fwd_t<N, float, double2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, s->d_tw1f, b, st);
-  else plane_fwd_t<N, float, float2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, s->d_tw1f, b, st);
+                        void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, const BatchRef& b,
+                        hipStream_t st) {
+  if (!mixed(s))
+    plane_fwd_t<N, double, double2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1, b, st);
+  else if (win_fp64)
+    plane_fwd_t<N, float, double2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1f, b, st);
+  else
+    plane_fwd_t<N, float, float2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1f, b, st);
 }
 
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
-                      void* acc, void* acc2, HMode mode, Taylor tay, hipStream_t st) {
+                      void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, hipStream_t st) {
   switch (s->n[1]) {
-#define KS_CASE(v) case v: plane_fwd_n<v, false>(s, nb, U, win, win_fp64, wout, acc, acc2, mode, tay, BatchRef{}, st); return true;
+#define KS_CASE(v) \
+  case v: plane_fwd_n<v, false>(s, nb, U, win, win_fp64, wout, acc, acc2, mode, tay, next, T, BatchRef{}, st); return true;
     KS_SIZES(KS_CASE)
 #undef KS_CASE
     default:
@@ -539,15 +558,30 @@ bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win
 }
 
 bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool win_fp64,
-                            Taylor tay, hipStream_t st) {
+                            Taylor tay, int next, hipStream_t st) {
   const BatchRef b{jobs, rows, nrows};
   switch (s->n[1]) {
-#define KS_CASE(v) case v: plane_fwd_n<v, true>(s, 0, nullptr, nullptr, win_fp64, nullptr, nullptr, nullptr, H_TAYLOR, tay, b, st); return true;
+#define KS_CASE(v)                                                                                              \
+  case v:                                                                                                       \
+    plane_fwd_n<v, true>(s, 0, nullptr, nullptr, win_fp64, nullptr, nullptr, nullptr, H_TAYLOR, tay, next, nullptr, b, st); \
+    return true;
     KS_SIZES(KS_CASE)
 #undef KS_CASE
     default:
       return false;
   }
+}
+
+// Whether the plane analysis goes on to the next synthesis: wherever
+// the coefficients of the G orbitals' plane fit the y-batch's LDS, which is
+// free by then.  It paid at every size and launch measured (see the kernel);
+// larger planes (wide spheres past 120) keep the two launches.
+bool plane_next(const ks_system* s) {
+  bool fits = false;
+  with_plane_cfg<true>(s, [&](auto c) {
+    fits = (size_t)decltype(c)::G * s->npp_max <= (size_t)decltype(c)::YB * (s->n[1] + 1);
+  });
+  return fits;
 }
 
 }  // namespace ks

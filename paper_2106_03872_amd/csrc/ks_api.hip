@@ -526,16 +526,26 @@ ks_status check_common(ks_system* s, int norb) {
   return KS_OK;
 }
 
+// How an H psi meets its neighbours in a chain: whether T already holds the
+// plane synthesis of its input, and what its plane analysis leaves there
+// (launch_plane_fwd's next).
+struct Chain {
+  bool have_t = false;
+  int next = 0;
+};
+
 // H applied to nb packed orbitals win; result per mode (see plane_fwd_kernel)
 // win_fp64: the input is the FP64 orbital state (else the working precision)
-// H applied to nb packed orbitals win.  With rho (only when natoms > 0), the
-// x-projection pass also writes (or adds, accumulate) the density
-// sum occ |win|^2 to rho.
+// With rho (only when natoms > 0), the x-projection pass also writes (or adds,
+// accumulate) the density sum occ |win|^2 to rho.
 ks_status hpsi_packed(ks_system* s, int nb, const void* win, bool win_fp64, void* wout, void* acc, HMode mode, Taylor tay,
                       hipStream_t st, const double* occ = nullptr, double* rho = nullptr, int accumulate = 0,
-                      void* acc2 = nullptr) {
-  ks_status r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, win, win_fp64, s->T, st); });
-  if (r != KS_OK) return r;
+                      void* acc2 = nullptr, Chain ch = Chain{}) {
+  ks_status r;
+  if (!ch.have_t &&
+      (r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, win, win_fp64, s->T, st); })) !=
+          KS_OK)
+    return r;
   const void* sums = nullptr;   // partial sums that the x-apply pass adds itself
   if (s->natoms > 0 && s->proj_mode == 1 && !rho) {
     r = kcall(s, KS_K_GPROJ, st, "gproj", [&] { return launch_gproj(s, nb, win, win_fp64, s->DP, st); });
@@ -553,13 +563,16 @@ ks_status hpsi_packed(ks_system* s, int nb, const void* win, bool win_fp64, void
   r = kcall(s, KS_K_XAPPLY, st, "xapply", [&] { return launch_xapply(s, nb, s->T, s->DP, sums, s->U, st); });
   if (r != KS_OK) return r;
   return kcall(s, KS_K_PLANE_FWD, st, "plane_fwd",
-               [&] { return launch_plane_fwd(s, nb, s->U, win, win_fp64, wout, acc, acc2, mode, tay, st); });
+               [&] { return launch_plane_fwd(s, nb, s->U, win, win_fp64, wout, acc, acc2, mode, tay, ch.next, s->T, st); });
 }
 
+// have_t: T already holds the plane synthesis of pk
 ks_status density_packed(ks_system* s, int nb, const void* pk, const double* occ, double* rho, int accumulate,
-                         hipStream_t st) {
-  ks_status r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, pk, true, s->T, st); });
-  if (r != KS_OK) return r;
+                         hipStream_t st, bool have_t = false) {
+  ks_status r;
+  if (!have_t &&
+      (r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, pk, true, s->T, st); })) != KS_OK)
+    return r;
   return kcall(s, KS_K_XDENS, st, "xdens", [&] { return launch_xdens(s, nb, s->T, occ, rho, accumulate, st); });
 }
 
@@ -587,6 +600,7 @@ ks_status taylor_packed(ks_system* s, int nb, double2* state, double dt, int nst
   taylor_coefficients(dt, coef);
   ks_status r;
   const bool fuse = rho && s->natoms > 0;
+  const bool chain = plane_next(s);   // plane analyses go on to the next synthesis
   for (int step = 0; step < nsteps; ++step) {
     // w1 = H psi -> pk1, w2 -> pk2, w3 -> pk1, w4 not stored; state += a_k w_k
     void* src[4] = {state, s->pk[1], s->pk[2], s->pk[1]};
@@ -595,12 +609,15 @@ ks_status taylor_packed(ks_system* s, int nb, double2* state, double dt, int nst
       Taylor tay{coef[k], k < 4 ? 1 : 0, {0.0, 0.0}};
       const bool in64 = k == 1 || s->prec == KS_FP64;
       double* rho_prev = (fuse && k == 1 && step > 0) ? rho + (size_t)(step - 1) * s->N : nullptr;
-      if ((r = hpsi_packed(s, nb, src[k - 1], in64, dst[k - 1], state, H_TAYLOR, tay, st, occ, rho_prev,
-                           accumulate)) != KS_OK)
+      Chain ch;
+      ch.have_t = chain && (k > 1 || step > 0);
+      if (chain) ch.next = k < 4 ? 1 : (rho || step < nsteps - 1) ? 2 : 0;
+      if ((r = hpsi_packed(s, nb, src[k - 1], in64, dst[k - 1], state, H_TAYLOR, tay, st, occ, rho_prev, accumulate,
+                           nullptr, ch)) != KS_OK)
         return r;
     }
     if (rho && (!fuse || step == nsteps - 1) &&
-        (r = density_packed(s, nb, state, occ, rho + (size_t)step * s->N, accumulate, st)) != KS_OK)
+        (r = density_packed(s, nb, state, occ, rho + (size_t)step * s->N, accumulate, st, chain)) != KS_OK)
       return r;
     if (norms && (r = kcall(s, KS_K_DOTS, st, "dots", [&] {
            return launch_dots(s, nb, state, nullptr, s->red, norms + (size_t)step * norms_stride, st);
@@ -664,8 +681,9 @@ ks_status etrs_packed(ks_system* s, ks_state* t, double dt, int nsteps, const do
       for (int k = 1; k <= 4; ++k) {
         Taylor tay{ch[k], k < 4 ? 1 : 0, cf[k]};
         const bool in64 = k == 1 || s->prec == KS_FP64;
-        if ((r = hpsi_packed(s, nb, src[k - 1], in64, dst[k - 1], slice, H_TAYLOR, tay, st, nullptr, nullptr, 0,
-                             pred)) != KS_OK)
+        const bool chain = plane_next(s);
+        if ((r = hpsi_packed(s, nb, src[k - 1], in64, dst[k - 1], slice, H_TAYLOR, tay, st, nullptr, nullptr, 0, pred,
+                             Chain{chain && k > 1, chain && k < 4 ? 1 : 0})) != KS_OK)
           return r;
       }
     }
@@ -2075,13 +2093,15 @@ static ks_status batch_taylor(ks_batch* b, double dt, int nsteps, hipStream_t st
   taylor_coefficients(dt, coef);
   ks_status r;
   // chunk-outer, step-inner, as a state stepped alone
+  const bool chain = plane_next(s0);   // plane analyses go on to the next synthesis
   for (const ks_batch_pass& bp : b->passes) {
     for (int step = 0; step < nsteps; ++step) {
       for (int k = 1; k <= 4; ++k) {
         const BatchJob* jobs = bp.jobs[k - 1];
         const bool in64 = k == 1 || s0->prec == KS_FP64;
         const Taylor tay{coef[k], k < 4 ? 1 : 0, {0.0, 0.0}};
-        if ((r = kcall(s0, KS_K_PLANE_INV, st, "plane_inv",
+        if (!(chain && (k > 1 || step > 0)) &&
+            (r = kcall(s0, KS_K_PLANE_INV, st, "plane_inv",
                        [&] {
                          return row_slices(bp.rows_p, bp.nrows_p, [&](const int4* rs, int n) {
                            return launch_plane_inv_batch(s0, jobs, rs, n, in64, st);
@@ -2113,7 +2133,8 @@ static ks_status batch_taylor(ks_batch* b, double dt, int nsteps, hipStream_t st
         if ((r = kcall(s0, KS_K_PLANE_FWD, st, "plane_fwd",
                        [&] {
                          return row_slices(bp.rows_p, bp.nrows_p, [&](const int4* rs, int n) {
-                           return launch_plane_fwd_batch(s0, jobs, rs, n, in64, tay, st);
+                           const int next = !chain ? 0 : k < 4 ? 1 : step < nsteps - 1 ? 2 : 0;
+                           return launch_plane_fwd_batch(s0, jobs, rs, n, in64, tay, next, st);
                          });
                        })) !=
             KS_OK)

@@ -286,8 +286,11 @@ bool launch_proj_reduce(const ks_system* s, int nb, const void* partial, double2
 bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP, const void* partial, void* U,
                    hipStream_t st);
 bool xapply_sums(const ks_system* s, long long values);
+// next (where plane_next says so): also the plane synthesis into T, 1 of the
+// H psi formed (wout), 2 of the accumulated state
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
-                      void* acc, void* acc2, HMode mode, Taylor tay, hipStream_t st);
+                      void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, hipStream_t st);
+bool plane_next(const ks_system* s);
 bool launch_xdens(const ks_system* s, int nb, const void* T, const double* occ, double* rho, int accumulate,
                   hipStream_t st);
 // Batched launches over several systems of s's grid (s supplies the sphere,
@@ -303,7 +306,7 @@ bool launch_x_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, 
 bool launch_proj_reduce_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, int max_natoms,
                               hipStream_t st);
 bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4* rows, int nrows, bool win_fp64,
-                            Taylor tay, hipStream_t st);
+                            Taylor tay, int next, hipStream_t st);
 // orbitals per block of the x-pencil and plane passes for a launch over
 // total_orbitals orbitals (the same rule as the single-system launches)
 int x_group_size(const ks_system* s, long long total_orbitals);
