@@ -34,6 +34,7 @@ HIPCC_FLAGS = [
 UNIT_FLAGS = {
     "k_xpass.hip": ["-fno-signed-zeros"],
     "k_plane.hip": ["-fno-signed-zeros"],
+    "k_plane_box.hip": ["-fno-signed-zeros"],
 }
 
 

@@ -534,18 +534,12 @@ struct Chain {
   int next = 0;
 };
 
-// H applied to nb packed orbitals win; result per mode (see plane_fwd_kernel)
-// win_fp64: the input is the FP64 orbital state (else the working precision)
-// With rho (only when natoms > 0), the x-projection pass also writes (or adds,
-// accumulate) the density sum occ |win|^2 to rho.
-ks_status hpsi_packed(ks_system* s, int nb, const void* win, bool win_fp64, void* wout, void* acc, HMode mode, Taylor tay,
-                      hipStream_t st, const double* occ = nullptr, double* rho = nullptr, int accumulate = 0,
-                      void* acc2 = nullptr, Chain ch = Chain{}) {
+// The x-passes of H psi, T -> U.  win: the packed input (of the reciprocal-space
+// projections, proj_mode 1).  With rho (only when natoms > 0), the x-projection
+// pass also writes (or adds, accumulate) the density sum occ |win|^2 to rho.
+ks_status x_passes(ks_system* s, int nb, const void* win, bool win_fp64, hipStream_t st, const double* occ, double* rho,
+                   int accumulate) {
   ks_status r;
-  if (!ch.have_t &&
-      (r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, win, win_fp64, s->T, st); })) !=
-          KS_OK)
-    return r;
   const void* sums = nullptr;   // partial sums that the x-apply pass adds itself
   if (s->natoms > 0 && s->proj_mode == 1 && !rho) {
     r = kcall(s, KS_K_GPROJ, st, "gproj", [&] { return launch_gproj(s, nb, win, win_fp64, s->DP, st); });
@@ -562,8 +556,30 @@ ks_status hpsi_packed(ks_system* s, int nb, const void* win, bool win_fp64, void
   }
   r = kcall(s, KS_K_XAPPLY, st, "xapply", [&] { return launch_xapply(s, nb, s->T, s->DP, sums, s->U, st); });
   if (r != KS_OK) return r;
+  return KS_OK;
+}
+
+// H applied to nb packed orbitals win; result per mode (see plane_fwd_kernel)
+// win_fp64: the input is the FP64 orbital state (else the working precision)
+ks_status hpsi_packed(ks_system* s, int nb, const void* win, bool win_fp64, void* wout, void* acc, HMode mode, Taylor tay,
+                      hipStream_t st, const double* occ = nullptr, double* rho = nullptr, int accumulate = 0,
+                      void* acc2 = nullptr, Chain ch = Chain{}) {
+  ks_status r;
+  if (!ch.have_t &&
+      (r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv(s, nb, win, win_fp64, s->T, st); })) !=
+          KS_OK)
+    return r;
+  if ((r = x_passes(s, nb, win, win_fp64, st, occ, rho, accumulate)) != KS_OK) return r;
   return kcall(s, KS_K_PLANE_FWD, st, "plane_fwd",
                [&] { return launch_plane_fwd(s, nb, s->U, win, win_fp64, wout, acc, acc2, mode, tay, ch.next, s->T, st); });
+}
+
+// H applied to nb orbitals in boxes (in and out apart); not for the
+// reciprocal-space projections, which read packed orbitals.
+ks_status hpsi_box(ks_system* s, int nb, const double2* in, double2* out, hipStream_t st) {
+  ks_status r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv_box(s, nb, in, s->T, st); });
+  if (r != KS_OK || (r = x_passes(s, nb, nullptr, true, st, nullptr, nullptr, 0)) != KS_OK) return r;
+  return kcall(s, KS_K_PLANE_FWD, st, "plane_fwd", [&] { return launch_plane_fwd_box(s, nb, s->U, in, out, st); });
 }
 
 // have_t: T already holds the plane synthesis of pk
@@ -1369,6 +1385,10 @@ ks_status ks_ham_apply(ks_system* s, int norb, const void* psi, void* hpsi, void
     const int nb = std::min(cl, norb - o0);
     const double2* in = (const double2*)psi + (size_t)o0 * s->N;
     double2* out = (double2*)hpsi + (size_t)o0 * s->N;
+    if (!(s->natoms > 0 && s->proj_mode == 1)) {
+      if ((r = hpsi_box(s, nb, in, out, st)) != KS_OK) return r;
+      continue;
+    }
     if ((r = kcall(s, KS_K_PACK, st, "pack", [&] { return launch_pack(s, nb, in, s->N, s->pk[0], st); })) != KS_OK) return r;
     if ((r = hpsi_packed(s, nb, s->pk[0], true, s->pk[1], nullptr, H_OUT, none, st)) != KS_OK) return r;
     const bool fp64 = s->prec == KS_FP64;
@@ -1416,8 +1436,10 @@ ks_status ks_density(ks_system* s, int norb, const void* psi, const double* occ,
   for (int o0 = 0; o0 < norb; o0 += cl) {
     const int nb = std::min(cl, norb - o0);
     const double2* box = (const double2*)psi + (size_t)o0 * s->N;
-    if ((r = kcall(s, KS_K_PACK, st, "pack", [&] { return launch_pack(s, nb, box, s->N, s->pk[0], st); })) != KS_OK) return r;
-    if ((r = density_packed(s, nb, s->pk[0], occ + o0, rho, o0 > 0, st)) != KS_OK) return r;
+    if ((r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv_box(s, nb, box, s->T, st); })) !=
+            KS_OK ||
+        (r = density_packed(s, nb, nullptr, occ + o0, rho, o0 > 0, st, true)) != KS_OK)
+      return r;
   }
   return KS_OK;
 }

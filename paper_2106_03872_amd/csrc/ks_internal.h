@@ -291,6 +291,9 @@ bool xapply_sums(const ks_system* s, long long values);
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
                       void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, hipStream_t st);
 bool plane_next(const ks_system* s);
+// the same from and to boxes (complex128 [n0][n1][n2] per orbital, the result zero outside the sphere)
+bool launch_plane_inv_box(const ks_system* s, int nb, const double2* box, void* T, hipStream_t st);
+bool launch_plane_fwd_box(const ks_system* s, int nb, const void* U, const double2* in, double2* out, hipStream_t st);
 bool launch_xdens(const ks_system* s, int nb, const void* T, const double* occ, double* rho, int accumulate,
                   hipStream_t st);
 // Batched launches over several systems of s's grid (s supplies the sphere,
