@@ -604,18 +604,37 @@ bool x_shape_available(int n0, int shape) {
 int x_shape_nb(int n0, int shape) { return shape == 1 || shape == 3 ? 16 : x_tile_nb(n0); }
 int x_shape_threads(int shape) { return shape == 1 || shape == 3 ? 192 : NT; }
 
+// Orbital groups of a density pass (ng) and where they write their partial
+// densities, which dens_sum adds in order: groups of at least DENS_GROUP
+// orbitals, at most `most` of them.  A launch that leaves more than half of the
+// compute units' block slots empty that way (fewer than 512 blocks: small
+// grids, few orbitals) takes more and smaller groups, as many as U, which is
+// written only after a density pass, holds (24^3, 10 orbitals, complex64: the
+// projections with the density took 14.9 us in 2 groups, 11.4 in 5).
+struct DensPlan {
+  int ng;
+  double* part;
+};
+static DensPlan dens_plan(const ks_system* s, int nb, int most) {
+  const int by_size = std::max(1, std::min(most, (nb + DENS_GROUP - 1) / DENS_GROUP));
+  const int by_fill = (512 + s->ntiles - 1) / s->ntiles;
+  const size_t es = mixed(s) ? sizeof(float2) : sizeof(double2);
+  const size_t fit = (size_t)s->cb * s->nplanes * es / ((size_t)s->n[0] * sizeof(double));
+  const int ng = (int)std::min<size_t>(fit, std::min(nb, std::min(most, by_fill)));
+  if (ng > by_size) return {ng, static_cast<double*>(s->U)};
+  return {by_size, s->dens_part};
+}
+
 template <int N0, bool HB>
 static void xproj_n(const ks_system* s, int nb, const void* T, void* partial, const double* occ, double* rho,
                     int accumulate, hipStream_t st) {
   const double scale = s->dV / sqrt(s->omega);
   const double inv_omega = 1.0 / s->omega;
   const bool dens = rho != nullptr;
-  // with the density: groups of at least DENS_GROUP orbitals, so the partial
-  // densities fit their buffer
-  const int ng = dens ? std::min(x_groups(s, nb), (nb + DENS_GROUP - 1) / DENS_GROUP) : x_groups(s, nb);
+  const DensPlan dp = dens ? dens_plan(s, nb, x_groups(s, nb)) : DensPlan{x_groups(s, nb), nullptr};
   with_shape<N0>(s, [&](auto sh) {
     using SH = decltype(sh);
-    const dim3 grid(s->ntiles, ng);
+    const dim3 grid(s->ntiles, dp.ng);
     if (!dens) {
       if (!mixed(s))
         xproj_kernel<N0, SH, double, HB, false><<<grid, SH::XT, 0, st>>>(
@@ -627,16 +646,16 @@ static void xproj_n(const ks_system* s, int nb, const void* T, void* partial, co
             inv_omega);
     } else if (!mixed(s)) {
       xproj_kernel<N0, SH, double, HB, true><<<grid, SH::XT, 0, st>>>(
-          (const double2*)T, nb, (double2*)partial, sphere_tab(s), proj_tab(s), s->d_tw0, scale, occ, s->dens_part,
+          (const double2*)T, nb, (double2*)partial, sphere_tab(s), proj_tab(s), s->d_tw0, scale, occ, dp.part,
           inv_omega);
     } else {
       xproj_kernel<N0, SH, float, HB, true><<<grid, SH::XT, 0, st>>>(
-          (const float2*)T, nb, (float2*)partial, sphere_tab(s), proj_tab(s), s->d_tw0f, scale, occ, s->dens_part,
+          (const float2*)T, nb, (float2*)partial, sphere_tab(s), proj_tab(s), s->d_tw0f, scale, occ, dp.part,
           inv_omega);
     }
   });
   if (dens)
-    dens_sum_kernel<<<(unsigned)((s->N + NT - 1) / NT), NT, 0, st>>>(s->dens_part, ng, s->N, rho, accumulate);
+    dens_sum_kernel<<<(unsigned)((s->N + NT - 1) / NT), NT, 0, st>>>(dp.part, dp.ng, s->N, rho, accumulate);
 }
 
 bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, const double* occ, double* rho,
@@ -751,42 +770,33 @@ int x_group_size(const ks_system* s, long long total_orbitals) {
   return (int)(g < 1 ? 1 : (g > s->xg_max ? s->xg_max : g));
 }
 
-// Orbital groups of the density pass: each group writes one partial density
-// that dens_sum adds in order, so the groups are as large as keeps about 12
-// blocks per CU busy, and hold at least DENS_GROUP orbitals.
-static int dens_groups(const ks_system* s, int nb) {
-  const int by_size = (nb + DENS_GROUP - 1) / DENS_GROUP;
-  const int by_fill = (256 * 12 + s->ntiles - 1) / s->ntiles;
-  return std::max(1, std::min(by_size, by_fill));
-}
-
 template <int N0, bool HB>
-static void xdens_n(const ks_system* s, int nb, const void* T, const double* occ, double* part, hipStream_t st) {
-  const int ng = dens_groups(s, nb);
+static void xdens_n(const ks_system* s, int nb, const void* T, const double* occ, const DensPlan& dp, hipStream_t st) {
   with_shape<N0>(s, [&](auto sh) {
     using SH = decltype(sh);
-    const dim3 grid(s->ntiles, ng);
+    const dim3 grid(s->ntiles, dp.ng);
     if (!mixed(s))
-      xdens_kernel<N0, SH, double, HB><<<grid, SH::XT, 0, st>>>((const double2*)T, nb, occ, part, sphere_tab(s),
+      xdens_kernel<N0, SH, double, HB><<<grid, SH::XT, 0, st>>>((const double2*)T, nb, occ, dp.part, sphere_tab(s),
                                                                s->d_tw0, 1.0 / s->omega);
     else
-      xdens_kernel<N0, SH, float, HB><<<grid, SH::XT, 0, st>>>((const float2*)T, nb, occ, part, sphere_tab(s),
+      xdens_kernel<N0, SH, float, HB><<<grid, SH::XT, 0, st>>>((const float2*)T, nb, occ, dp.part, sphere_tab(s),
                                                               s->d_tw0f, 1.0 / s->omega);
   });
 }
 
 bool launch_xdens(const ks_system* s, int nb, const void* T, const double* occ, double* rho, int accumulate,
                   hipStream_t st) {
+  // at most about 12 blocks per CU
+  const DensPlan dp = dens_plan(s, nb, (256 * 12 + s->ntiles - 1) / s->ntiles);
   switch (s->n[0]) {
 #define KS_CASE(v) \
-  case v: s->x_half ? xdens_n<v, true>(s, nb, T, occ, s->dens_part, st) : xdens_n<v, false>(s, nb, T, occ, s->dens_part, st); break;
+  case v: s->x_half ? xdens_n<v, true>(s, nb, T, occ, dp, st) : xdens_n<v, false>(s, nb, T, occ, dp, st); break;
     KS_SIZES(KS_CASE)
 #undef KS_CASE
     default:
       return false;
   }
-  const int ng = dens_groups(s, nb);
-  dens_sum_kernel<<<(unsigned)((s->N + NT - 1) / NT), NT, 0, st>>>(s->dens_part, ng, s->N, rho, accumulate);
+  dens_sum_kernel<<<(unsigned)((s->N + NT - 1) / NT), NT, 0, st>>>(dp.part, dp.ng, s->N, rho, accumulate);
   return true;
 }
 
