@@ -13,7 +13,6 @@ namespace {
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) { return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ __forceinline__ double2 cconj(double2 a) { return double2{a.x, -a.y}; }
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return double2{a.x + b.x, a.y + b.y}; }
-__device__ __forceinline__ double2 cscale(double2 a, double s) { return double2{a.x * s, a.y * s}; }
 
 // ---------------------------------------------------------- Jacobi rotations
 //
@@ -47,129 +46,190 @@ constexpr int BJ_ST = 512;          // threads of a solve block: one half works 
 static_assert(2 * BJ_B * BJ_B == BJ_ST, "one thread per 2x2 block of S and one per 2x2 of U");
 
 // Rotation J (2x2, acting on indices p < q) with (J^H A J)_pq = 0 for the
-// Hermitian block [[a, b], [conj(b), c]]: with b = |b| e^{i phi}, the phase
-// D = diag(1, e^{-i phi}) makes the block real, and the real symmetric
-// rotation [[cs, sn], [-sn, cs]] with t = tan(theta) the smaller root of
-// t^2 + 2 tau t - 1 = 0, tau = (c - a) / (2|b|), zeroes it; J = D R, i.e.
-//   J = [[cs, sn], [-f, g]],  f = sn e, g = cs e,  e = e^{-i phi}.
-// With h = |tau| + sqrt(1 + tau^2) = 1/|t|: cs = h / sqrt(1 + h^2) and
-// sn = sign(tau) / sqrt(1 + h^2), with sqrt(x) = x rsqrt(x) for x >= 1, so the
-// chain has three reciprocal square roots and no division.  An element so small against
-// the diagonal gap that h^2 would overflow is left alone (the rotation angle
-// would be below 1e-150).
+// Hermitian block [[a, b], [conj(b), c]], of the smaller angle:
+//   J = [[cs, conj(f)], [-f, cs]],  f = sn conj(b) / |b|,
+// with d = (c - a) / 2, r = sqrt(d^2 + |b|^2): cs^2 = (1 + |d| / r) / 2 and
+// sn = sign(d) |b| / (2 r cs).  Two reciprocal square roots in a chain and no
+// division.  (The columns' phases are free: eig_finish sets them.)  An element
+// whose square underflows, or a block whose gap's overflows, is left alone.
 struct Rot {
-  double cs, sn;
-  double2 f, g;
+  double cs;
+  double2 f;
 };
 
 __device__ __forceinline__ Rot make_rot(double a, double c, double2 b) {
-  Rot r{1.0, 0.0, double2{0.0, 0.0}, double2{1.0, 0.0}};
   const double b2 = b.x * b.x + b.y * b.y;
-  if (b2 == 0.0) return r;
-  const double rb = rsqrt(b2);   // 1 / |b|
-  const double tau = 0.5 * (c - a) * rb;
-  const double at = fabs(tau);
-  if (!(at < 1e150)) return r;
-  const double q = fma(tau, tau, 1.0);
-  const double h = at + q * rsqrt(q);
-  const double rh = rsqrt(fma(h, h, 1.0));
-  r.cs = h * rh;
-  r.sn = tau >= 0.0 ? rh : -rh;
-  const double2 e{b.x * rb, -b.y * rb};
-  r.f = cscale(e, r.sn);
-  r.g = cscale(e, r.cs);
-  return r;
+  const double d = 0.5 * (c - a);
+  const double x = fma(d, d, b2);
+  if (b2 == 0.0 || !(x < 1e300)) return Rot{1.0, double2{0.0, 0.0}};
+  const double ir = 0.5 * rsqrt(x);   // 1 / 2r
+  const double u = fma(fabs(d), ir, 0.5);
+  const double ic = rsqrt(u);         // 1 / cs
+  const double w = copysign(ir * ic, d);
+  return Rot{u * ic, double2{b.x * w, -b.y * w}};
 }
 
 // (x0, x1) J: the row vector (x0, x1) times the rotation
 __device__ __forceinline__ void rot_right(const Rot& r, double2 x0, double2 x1, double2& y0, double2& y1) {
-  const double2 a = cmul(x1, r.f), b = cmul(x1, r.g);
+  const double2 a = cmul(x1, r.f), b = cmul(x0, cconj(r.f));
   y0 = double2{r.cs * x0.x - a.x, r.cs * x0.y - a.y};
-  y1 = double2{r.sn * x0.x + b.x, r.sn * x0.y + b.y};
+  y1 = double2{r.cs * x1.x + b.x, r.cs * x1.y + b.y};
 }
 
 // J^H (x0, x1)^T: the rotation's adjoint times the column vector (x0, x1)
 __device__ __forceinline__ void rot_left_adj(const Rot& r, double2 x0, double2 x1, double2& y0, double2& y1) {
-  const double2 a = cmul(cconj(r.f), x1), b = cmul(cconj(r.g), x1);
+  const double2 a = cmul(cconj(r.f), x1), b = cmul(r.f, x0);
   y0 = double2{r.cs * x0.x - a.x, r.cs * x0.y - a.y};
-  y1 = double2{r.sn * x0.x + b.x, r.sn * x0.y + b.y};
+  y1 = double2{r.cs * x1.x + b.x, r.cs * x1.y + b.y};
 }
+
+// the rotation that lane src of the wave holds
+__device__ __forceinline__ Rot rot_of(const Rot& r, int src) {
+  return Rot{__shfl(r.cs, src, 64), double2{__shfl(r.f.x, src, 64), __shfl(r.f.y, src, 64)}};
+}
+
+// v of the next lane, cyclic within rows of 16 lanes
+__device__ __forceinline__ double next_lane(double v) {
+  const long long i = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)i, 0x12f, 0xf, 0xf, false);   // row_ror:15
+  const int hi = __builtin_amdgcn_mov_dpp((int)(i >> 32), 0x12f, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double2 next_lane(double2 v) { return double2{next_lane(v.x), next_lane(v.y)}; }
 
 // global index of local index l of block pair (I, J)
 __device__ __forceinline__ int bj_index(int I, int J, int l) { return l < BJ_B ? I * BJ_B + l : J * BJ_B + (l - BJ_B); }
 
-// Block k of round t: rotations of the sub-problem of block pair k (ALL: every
-// index pair, else the pairs across the two blocks); its unitary goes to
-// Ublk[k] (row-major BJ_M x BJ_M).  S and U are kept in two LDS copies: inner
-// round r reads one and writes the other (every entry is rewritten), so a
-// round needs one barrier.
+// Block k of round t: rotations of the sub-problem S of block pair k (ALL: every
+// index pair, else the pairs across the two blocks); its unitary U goes to
+// Ublk[k] (row-major BJ_M x BJ_M).  Thread (P, Q) of the first half forms the
+// rotation of the inner round's pair Q, takes that of pair P from its row's lane
+// P, and updates the 2x2 block (P, Q) of S; of the second half rows P and P +
+// BJ_B of U, columns of pair Q.
 //
-// Bound: the latency of an inner round, a serial chain of LDS reads, the
-// rotation's formation, two 2x2 products and the barrier, on one workgroup
-// per block pair.  A lone wave per SIMD issues a vector instruction only every
-// eight to ten cycles, so the U update has waves of its own.  A full sweep (31
-// inner rounds, 256 threads) in every round took 34.4 us per round and 7.5
-// sweeps (n = 128); now 14.7 us (33.3 us in round 0) and 8.5 sweeps.
+// Across the blocks (inner round r pairs index i with BJ_B + (i + r) mod BJ_B)
+// a thread's entries stay in registers: the columns BJ_B + ... move by one lane
+// per round, the rows by one row of threads, through LDS (two copies, so a round
+// needs one barrier) together with the entries that the next rotations are
+// formed from.  With ALL pairs S and U are kept in two LDS copies.
+//
+// Bound: the latency of an inner round on one workgroup per block pair: LDS
+// reads, the rotation's formation, two 2x2 products, about 120 vector
+// instructions of a wave that has its SIMD almost alone and so issues one every
+// eight cycles, and the barrier.  A full sweep (31 inner rounds) with S and U in
+// LDS in every round took 34.4 us per round (n = 128), the pairs across alone
+// 14.5 us; 10.1 us now (round 0: 33.2 and 27.1 us).
 template <bool ALL>
 __global__ __launch_bounds__(BJ_ST) void bj_solve_kernel(const double2* __restrict__ A, int N2, int t,
                                                          double2* __restrict__ Ublk) {
-  __shared__ double2 S[2][BJ_M][BJ_M + 1];
-  __shared__ double2 U[2][BJ_M][BJ_M + 1];
   const int k = blockIdx.x, tid = threadIdx.x;
+  const bool on_s = tid < BJ_B * BJ_B;   // uniform per wave
+  const int P = (tid / BJ_B) % BJ_B, Q = tid % BJ_B;
+  const int lane_p = (tid & 48) + P;     // lane of this row of 16 that forms the rotation of pair P
   int I, J;
   round_pair(t, k, N2 / BJ_B, I, J);
-  for (int e = tid; e < BJ_M * BJ_M; e += BJ_ST) {
-    const int r = e / BJ_M, c = e % BJ_M;
-    S[0][r][c] = A[(long long)bj_index(I, J, r) * N2 + bj_index(I, J, c)];
-    U[0][r][c] = double2{r == c ? 1.0 : 0.0, 0.0};
-  }
-  __syncthreads();
-  const bool on_s = tid < BJ_B * BJ_B;   // uniform per wave
-  const int P2 = (tid / BJ_B) % BJ_B, Q2 = tid % BJ_B;
-  auto pair_of = [](int r, int i, int& p, int& q) {
-    if constexpr (ALL) {
-      round_pair(r, i, BJ_M, p, q);
-    } else {
-      p = i;
-      q = BJ_B + ((i + r) & (BJ_B - 1));
-    }
-  };
-  int cur = 0;
-  for (int r = 0; r < (ALL ? BJ_M - 1 : BJ_B); ++r) {
-    // every thread forms the rotations it applies itself from the current
-    // copy, so no barrier publishes them; its entries are read before, so
-    // their LDS latency overlaps
-    int k0, k1;
-    pair_of(r, Q2, k0, k1);
-    const int nx = cur ^ 1;
-    const double ka = S[cur][k0][k0].x, kc = S[cur][k1][k1].x;
-    const double2 kb = S[cur][k0][k1];
-    if (on_s) {
-      // 2x2 block (P2, Q2) of S <- J^H S J
-      int i0, i1;
-      pair_of(r, P2, i0, i1);
-      const double ia = S[cur][i0][i0].x, ic = S[cur][i1][i1].x;
-      const double2 ib = S[cur][i0][i1];
-      const double2 s00 = S[cur][i0][k0], s01 = S[cur][i0][k1], s10 = S[cur][i1][k0], s11 = S[cur][i1][k1];
-      const Rot rk = make_rot(ka, kc, kb), ri = make_rot(ia, ic, ib);
-      double2 t00, t01, t10, t11;
-      rot_right(rk, s00, s01, t00, t01);
-      rot_right(rk, s10, s11, t10, t11);
-      rot_left_adj(ri, t00, t10, S[nx][i0][k0], S[nx][i1][k0]);
-      rot_left_adj(ri, t01, t11, S[nx][i0][k1], S[nx][i1][k1]);
-    } else {
-      // rows P2 and P2 + BJ_B of U <- U J, columns of pair Q2
-      const double2 u00 = U[cur][P2][k0], u01 = U[cur][P2][k1];
-      const double2 u10 = U[cur][P2 + BJ_B][k0], u11 = U[cur][P2 + BJ_B][k1];
-      const Rot rk = make_rot(ka, kc, kb);
-      rot_right(rk, u00, u01, U[nx][P2][k0], U[nx][P2][k1]);
-      rot_right(rk, u10, u11, U[nx][P2 + BJ_B][k0], U[nx][P2 + BJ_B][k1]);
+  double2* out = Ublk + (long long)k * BJ_M * BJ_M;
+  if constexpr (ALL) {
+    __shared__ double2 S[2][BJ_M][BJ_M + 1];
+    __shared__ double2 U[2][BJ_M][BJ_M + 1];
+    for (int e = tid; e < BJ_M * BJ_M; e += BJ_ST) {
+      const int r = e / BJ_M, c = e % BJ_M;
+      S[0][r][c] = A[(long long)bj_index(I, J, r) * N2 + bj_index(I, J, c)];
+      U[0][r][c] = double2{r == c ? 1.0 : 0.0, 0.0};
     }
     __syncthreads();
-    cur = nx;
+    int cur = 0;
+    for (int r = 0; r < BJ_M - 1; ++r) {
+      int k0, k1;
+      round_pair(r, Q, BJ_M, k0, k1);
+      const int nx = cur ^ 1;
+      const double ka = S[cur][k0][k0].x, kc = S[cur][k1][k1].x;
+      const double2 kb = S[cur][k0][k1];
+      if (on_s) {
+        int i0, i1;
+        round_pair(r, P, BJ_M, i0, i1);
+        const double2 s00 = S[cur][i0][k0], s01 = S[cur][i0][k1], s10 = S[cur][i1][k0], s11 = S[cur][i1][k1];
+        const Rot rk = make_rot(ka, kc, kb), ri = rot_of(rk, lane_p);
+        double2 t00, t01, t10, t11;
+        rot_right(rk, s00, s01, t00, t01);
+        rot_right(rk, s10, s11, t10, t11);
+        rot_left_adj(ri, t00, t10, S[nx][i0][k0], S[nx][i1][k0]);
+        rot_left_adj(ri, t01, t11, S[nx][i0][k1], S[nx][i1][k1]);
+      } else {
+        const double2 u00 = U[cur][P][k0], u01 = U[cur][P][k1];
+        const double2 u10 = U[cur][P + BJ_B][k0], u11 = U[cur][P + BJ_B][k1];
+        const Rot rk = make_rot(ka, kc, kb);
+        rot_right(rk, u00, u01, U[nx][P][k0], U[nx][P][k1]);
+        rot_right(rk, u10, u11, U[nx][P + BJ_B][k0], U[nx][P + BJ_B][k1]);
+      }
+      __syncthreads();
+      cur = nx;
+    }
+    for (int e = tid; e < BJ_M * BJ_M; e += BJ_ST) out[e] = U[cur][e / BJ_M][e % BJ_M];
+  } else {
+    __shared__ double2 rows[2][2][BJ_B][BJ_B];   // the lower entries of S, to the thread row above
+    __shared__ double2 rot_ac[2][BJ_B], rot_b[2][BJ_B];   // diagonal entries and element of each pair
+    // x00 .. x11: entries (P, Q), (P, BJ_B + (Q + r)), (BJ_B + (P + r), Q), (BJ_B + (P + r), BJ_B + (Q + r))
+    // of S, indices mod BJ_B; of U with P for P + r
+    double2 x00, x01, x10, x11;
+    if (on_s) {
+      const double2* r0 = A + (long long)(I * BJ_B + P) * N2 + Q;
+      const double2* r1 = A + (long long)(J * BJ_B + P) * N2 + Q;
+      x00 = r0[I * BJ_B];
+      x01 = r0[J * BJ_B];
+      x10 = r1[I * BJ_B];
+      x11 = r1[J * BJ_B];
+      if (P == Q) {
+        rot_ac[0][P] = double2{x00.x, x11.x};
+        rot_b[0][P] = x01;
+      }
+    } else {
+      x00 = x11 = double2{P == Q ? 1.0 : 0.0, 0.0};
+      x01 = x10 = double2{0.0, 0.0};
+    }
+    __syncthreads();
+    int cur = 0;
+    for (int r = 0; r < BJ_B; ++r) {
+      const int nx = cur ^ 1;
+      const double2 ac = rot_ac[cur][Q], b = rot_b[cur][Q];
+      if (on_s && r > 0) {
+        x10 = rows[cur][0][(P + 1) % BJ_B][Q];
+        x11 = rows[cur][1][(P + 1) % BJ_B][Q];
+      }
+      const Rot rk = make_rot(ac.x, ac.y, b);
+      double2 t00, t01, t10, t11;
+      rot_right(rk, x00, x01, t00, t01);
+      rot_right(rk, x10, x11, t10, t11);
+      if (on_s) {
+        const Rot ri = rot_of(rk, lane_p);
+        rot_left_adj(ri, t00, t10, x00, x10);
+        rot_left_adj(ri, t01, t11, x01, x11);
+        const double c = x11.x;
+        x01 = next_lane(x01);
+        x11 = next_lane(x11);
+        rows[nx][0][P][Q] = x10;
+        rows[nx][1][P][Q] = x11;
+        if (P == Q) {
+          rot_ac[nx][P].x = x00.x;
+          rot_ac[nx][(P + BJ_B - 1) % BJ_B].y = c;
+          rot_b[nx][P] = x01;
+        }
+      } else {
+        x00 = t00;
+        x01 = next_lane(t01);
+        x10 = t10;
+        x11 = next_lane(t11);
+      }
+      __syncthreads();
+      cur = nx;
+    }
+    if (!on_s) {   // BJ_B moves: the columns are back in their places
+      out[P * BJ_M + Q] = x00;
+      out[P * BJ_M + BJ_B + Q] = x01;
+      out[(P + BJ_B) * BJ_M + Q] = x10;
+      out[(P + BJ_B) * BJ_M + BJ_B + Q] = x11;
+    }
   }
-  double2* out = Ublk + (long long)k * BJ_M * BJ_M;
-  for (int e = tid; e < BJ_M * BJ_M; e += BJ_ST) out[e] = U[cur][e / BJ_M][e % BJ_M];
 }
 
 constexpr int BJ_VCOLS = 64;   // columns of V per block of the V update
