@@ -80,6 +80,21 @@ __global__ __launch_bounds__(NT) void unpack_kernel(const T* __restrict__ pk, in
   }
 }
 
+// Block = wave of projection lanes; thread = lane.
+__global__ __launch_bounds__(64) void lane_rows_kernel(const int4* __restrict__ item, const int* __restrict__ lane_off,
+                                                       const int* __restrict__ pt_lds, const double* __restrict__ beta,
+                                                       int np, int n0, unsigned short* __restrict__ lane_pos,
+                                                       double* __restrict__ lane_beta) {
+  const int w = blockIdx.x, lane = threadIdx.x;
+  const int4 it = item[(long long)w * 64 + lane];
+  const int q = it.z % np;
+  for (int r = lane_off[w], k = it.x; r < lane_off[w + 1]; ++r, ++k) {
+    const bool in = k < it.y;
+    lane_pos[(long long)r * 64 + lane] = (unsigned short)(in ? pt_lds[k] : n0);
+    lane_beta[(long long)r * 64 + lane] = in ? beta[(long long)k * np + q] : 0.0;
+  }
+}
+
 // KB projections: P_Ip = sum over the (tile, atom) slots of atom I in
 // ascending tile order, DP = scale d_Ip P_Ip (Eq. vnl; scale is the analysis
 // normalisation that the x-analysis leaves out).  One wavefront per (atom,
@@ -220,6 +235,11 @@ bool launch_unpack(const ks_system* s, int nb, const void* pk, bool pk_fp64, dou
     default:
       return false;
   }
+}
+
+void launch_lane_rows(int nwaves, const int4* item, const int* lane_off, const int* pt_lds, const double* beta, int np,
+                      int n0, unsigned short* lane_pos, double* lane_beta, hipStream_t st) {
+  lane_rows_kernel<<<nwaves, 64, 0, st>>>(item, lane_off, pt_lds, beta, np, n0, lane_pos, lane_beta);
 }
 
 bool launch_proj_reduce(const ks_system* s, int nb, const void* partial, double2* DP, hipStream_t st) {

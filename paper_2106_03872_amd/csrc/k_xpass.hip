@@ -115,6 +115,8 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
   FR pre;
   if (oa < ob) load_inputs(pre, pos, Tin + oa * tstride, tbytes);
   const int4 item = pt.item[(long long)tile * XT + tid];
+  const int wave = __builtin_amdgcn_readfirstlane(tile * (XT / 64) + tid / 64);
+  const int row0 = pt.lane_off[wave], nrow = pt.lane_off[wave + 1] - row0;   // this wave's rows
   const int sA = pt.slot_off[tile], ns = pt.slot_off[tile + 1] - sA;
   if (!DENS && ns == 0) return;  // no sphere point in this tile (uniform per block)
   stage_twiddles<N0, XT, SH::V>(tw, tw0);
@@ -125,36 +127,33 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
 #pragma unroll
       for (int q = 0; q < LS::radix; ++q) a[it][q] = 0.0;
   }
-  // Projections: each lane sums beta * psi over its rows [ka, kb) of one
-  // (slot, projector) pair of the tile (in point order); the 2^g lanes of a
+  // Projections: each lane sums beta * psi over its rows of one (slot,
+  // projector) pair of the tile (in point order); the 2^g lanes of a
   // pair, adjacent and aligned, are then added by a fixed butterfly and the
   // group's first lane writes the pair (work planned per tile on the host).
   // (the host plans XT projection lanes per tile)
   const int np = pt.nproj;
-  const int ka = item.x, kb = item.y;
-  const int kq = item.z % np;
   const int glanes = 1 << (item.w & 0xff);
   const bool writer = (item.w & 256) != 0;
-  // The first KP points of the item (LDS position, beta) are the same for
-  // all orbitals of the block and stay in registers.
-  // Points a lane lacks read the unused last word of the first pencil's row
-  // (zero) with beta = 0, so that the reads of KPG points are in flight
-  // together instead of one behind each lane's own bound; groups that no lane
-  // of the wave has are skipped.
-  constexpr int KP = KB_CACHED_POINTS, KPG = 4;
+  // The first KP rows of the lanes (LDS position, beta) are the same for all
+  // orbitals of the block and stay in registers.  Rows are read in groups of
+  // KPG, with one coalesced load of each array per row (see build_proj); rows a
+  // lane lacks add beta = 0 times the unused last word of the first pencil's row
+  // (zero).
+  constexpr int KP = KB_CACHED_POINTS, KPG = KB_ROW_GROUP;
   static_assert(KP % KPG == 0, "whole groups");
+  const unsigned short* const lpos = pt.lane_pos + (long long)row0 * 64 + (tid & 63);
+  const double* const lbeta = pt.lane_beta + (long long)row0 * 64 + (tid & 63);
   int cpos[KP];
   double cbeta[KP];
   if (tid == 0) X[N0] = czero<C>();
-  const int k0 = DENS && ns == 0 ? 0 : pt.slot_pt[sA];   // a row of the tile
 #pragma unroll
   for (int g = 0; g < KP; g += KPG) {
-    if (__any(ka + g < kb)) {
+    if (g < nrow) {
 #pragma unroll
       for (int c = g; c < g + KPG; ++c) {
-        const int k = ka + c < kb ? ka + c : k0;
-        cpos[c] = pt.pt_lds[k];
-        cbeta[c] = pt.beta[(long long)k * np + kq];
+        cpos[c] = lpos[c * 64];
+        cbeta[c] = lbeta[c * 64];
       }
     } else {
 #pragma unroll
@@ -163,12 +162,6 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
         cbeta[c] = 0.0;
       }
     }
-  }
-#pragma unroll
-  for (int c = 0; c < KP; ++c) {   // after all loads are issued
-    const bool in = ka + c < kb;
-    cpos[c] = in ? cpos[c] : N0;
-    cbeta[c] = in ? cbeta[c] : 0.0;
   }
   C* pout = partial + item.z;
   const long long pstride = (long long)pt.nslots * np;
@@ -193,7 +186,7 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
     double sx = 0.0, sy = 0.0;
 #pragma unroll
     for (int g = 0; g < KP; g += KPG) {
-      if (__any(ka + g < kb)) {
+      if (g < nrow) {
         C x[KPG];
 #pragma unroll
         for (int c = 0; c < KPG; ++c) x[c] = X[cpos[g + c]];
@@ -204,11 +197,20 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
         }
       }
     }
-    for (int k = ka + KP; k < kb; ++k) {
-      const double bv = pt.beta[(long long)k * np + kq];
-      const C x = X[pt.pt_lds[k]];
-      sx += bv * double(x.x);
-      sy += bv * double(x.y);
+    for (int k = KP; k < nrow; k += KPG) {
+      int p[KPG];
+      double bv[KPG];
+#pragma unroll
+      for (int c = 0; c < KPG; ++c) {
+        p[c] = lpos[(k + c) * 64];
+        bv[c] = lbeta[(k + c) * 64];
+      }
+#pragma unroll
+      for (int c = 0; c < KPG; ++c) {
+        const C x = X[p[c]];
+        sx += bv[c] * double(x.x);
+        sy += bv[c] * double(x.y);
+      }
     }
     // the group's lanes add their sums by a fixed butterfly (the partners of
     // stage m: lane pairs of a quad, then quads, then mirrored halves of 8 and

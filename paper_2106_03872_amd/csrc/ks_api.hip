@@ -279,6 +279,7 @@ struct ProjHost {
   std::vector<int> pt_lds, slot_off, slot_atom, slot_pt, atom_slot_off, slot_pos;
   std::vector<int> up_off, up_lds, up_ent, ent_slot, ent_brow;
   std::vector<int4> item;
+  std::vector<int> lane_off;
 };
 
 ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, const int* npts, const int* idx,
@@ -319,13 +320,30 @@ ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, 
       pts.push_back(Pt{p / NB, p, I, (int)(f / npl), (int)off});
     }
   }
-  // projection side: order (tile, atom, pencil, j0)
-  std::stable_sort(pts.begin(), pts.end(), [](const Pt& a, const Pt& b) {
-    if (a.tile != b.tile) return a.tile < b.tile;
-    if (a.atom != b.atom) return a.atom < b.atom;
-    if (a.p != b.p) return a.p < b.p;
-    return a.j0 < b.j0;
-  });
+  // projection side: order (tile, atom, pencil, j0), points given twice in input
+  // order: each atom's points by (pencil, j0), then dealt out to the tiles (keys
+  // of 51 bits; sorting all points by comparison took twice as long)
+  std::vector<int> tile_pt(nt + 1, 0);   // first point of each tile
+  {
+    std::vector<unsigned long long> key;
+    std::vector<Pt> sorted(pts.size());
+    for (const Pt& q : pts) tile_pt[q.tile + 1]++;
+    for (int t = 0; t < nt; ++t) tile_pt[t + 1] += tile_pt[t];
+    std::vector<int> fill(tile_pt.begin(), tile_pt.end() - 1);
+    size_t a0 = 0;
+    for (int I = 0; I < natoms; ++I) {
+      key.resize(npts[I]);
+      for (int j = 0; j < npts[I]; ++j)
+        key[j] = ((unsigned long long)pts[a0 + j].p * n[0] + pts[a0 + j].j0) << 30 | (unsigned)j;
+      std::sort(key.begin(), key.end());
+      for (const unsigned long long k : key) {
+        const Pt& q = pts[a0 + (k & ((1ull << 30) - 1))];
+        sorted[fill[q.tile]++] = q;
+      }
+      a0 += npts[I];
+    }
+    pts.swap(sorted);
+  }
   h.brows.assign((size_t)total * np, 0.0);
   h.brow_input.assign(total, 0);
   h.pt_lds.assign(total, 0);
@@ -365,7 +383,9 @@ ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, 
   // orbitals; when a tile would need more lanes than the block has, the
   // largest groups are halved (their lanes then loop over extra rows).
   // item = (first row, end row, output index, g | 256 for the group's first
-  // lane).  An orbital's partial sums are ordered by atom (then tile), so an
+  // lane).  The rows of a wave's lanes are laid out lane by lane on the device
+  // (launch_lane_rows), from row lane_off of the wave to that of the next: the
+  // longest lane's rows rounded up to KB_ROW_GROUP.  An orbital's partial sums are ordered by atom (then tile), so an
   // atom's sums are contiguous: output index = slot_pos * nproj + projector.
   h.atom_slot_off.assign(natoms + 1, 0);
   h.slot_pos.assign(nslots, 0);
@@ -376,6 +396,8 @@ ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, 
     for (int k = 0; k < nslots; ++k) h.slot_pos[k] = fill[h.slot_atom[k]]++;
   }
   h.item.assign((size_t)nt * lanes, make_int4(0, 0, 0, 0));
+  const int waves = lanes / 64;
+  h.lane_off.assign((size_t)nt * waves + 1, 0);
   for (int t = 0; t < nt; ++t) {
     const int s0 = h.slot_off[t], ns = h.slot_off[t + 1] - s0;
     std::vector<int> lg(ns, 0);
@@ -405,18 +427,31 @@ ks_status build_proj(const int n[3], int xnb, int lanes, int natoms, int nproj, 
               make_int4(k0 + (int)((long long)len * sg / g), k0 + (int)((long long)len * (sg + 1) / g),
                         h.slot_pos[s0 + j] * np + q, lg[j] | (sg == 0 ? 256 : 0));
     }
+    for (int w = 0; w < waves; ++w) {
+      const int4* it = h.item.data() + (size_t)t * lanes + 64 * w;
+      int rows = 0;
+      for (int l = 0; l < 64; ++l) rows = std::max(rows, it[l].y - it[l].x);
+      rows = (rows + KB_ROW_GROUP - 1) / KB_ROW_GROUP * KB_ROW_GROUP;
+      const long long end = (long long)h.lane_off[(size_t)t * waves + w] + rows;
+      if (end > INT_MAX) {
+        err = "projector tables exceed the index range";
+        return KS_EUNSUPPORTED;
+      }
+      h.lane_off[(size_t)t * waves + w + 1] = (int)end;
+    }
   }
   // scatter side: order (tile, pencil, j0, atom); one entry per (point, atom)
   std::vector<int> order(pts.size());
-  for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-    const Pt& x = pts[a];
-    const Pt& y = pts[b];
-    if (x.tile != y.tile) return x.tile < y.tile;
-    if (x.p != y.p) return x.p < y.p;
-    if (x.j0 != y.j0) return x.j0 < y.j0;
-    return x.atom < y.atom;
-  });
+  {
+    std::vector<unsigned long long> key;
+    for (int t = 0; t < nt; ++t) {
+      key.clear();
+      for (int k = tile_pt[t]; k < tile_pt[t + 1]; ++k)
+        key.push_back(((unsigned long long)(pts[k].p - t * NB) * n[0] + pts[k].j0) << 32 | (unsigned)k);
+      std::sort(key.begin(), key.end());
+      for (size_t i = 0; i < key.size(); ++i) order[tile_pt[t] + i] = (int)(key[i] & 0xffffffffull);
+    }
+  }
   h.up_off.assign(nt + 1, 0);
   for (size_t i = 0; i < order.size(); ++i) {
     const Pt& q = pts[order[i]];
@@ -1083,9 +1118,9 @@ void ks_system_destroy(ks_system* s) {
   free_workspace(s);
   free_gtab(s, s->gp);
   void* ptrs[] = {s->d_plane_col0, s->d_plane_m1lo, s->d_col_off, s->d_col_m2lo, s->d_tw0, s->d_tw1,
-                  s->d_tw0f, s->d_tw1f, s->d_v, s->d_vloc, s->d_kin, s->d_hbox, s->d_rho_w, s->d_pt_lds, s->d_slot_off, s->d_slot_desc, s->d_slot_pt,
+                  s->d_tw0f, s->d_tw1f, s->d_v, s->d_vloc, s->d_kin, s->d_hbox, s->d_rho_w, s->d_lane_pos, s->d_slot_off, s->d_slot_desc, s->d_lane_off,
                   s->d_atom_slot_off,
-                  s->d_up_off, s->d_up_key, s->d_up_x, s->d_x_slot, s->d_beta, s->d_up_beta, s->d_x_beta, s->d_item,
+                  s->d_up_off, s->d_up_key, s->d_up_x, s->d_x_slot, s->d_lane_beta, s->d_up_beta, s->d_x_beta, s->d_item,
                   s->d_kb, s->red, s->ortho_pk, s->ortho_S, s->ortho_W, s->ortho_info, s->ortho_diag, s->gemm_part};
   for (void* p : ptrs) dfree(s, p);
   if (s->done) (void)hipEventDestroy(s->done);
@@ -1115,6 +1150,44 @@ ks_status ks_system_set_vloc(ks_system* s, const double* v, void* stream) {
   KS_HIP(s, hipMemcpyAsync(s->d_v, v, s->N * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
   KS_HIP(s, hipMemcpyAsync(s->d_vloc, v, s->N * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
   s->have_v = true;
+  return KS_OK;
+}
+
+// The lane-by-lane copies of the projection rows: laid out on the device from
+// the rows in T, which no work uses while the projectors are set, so that the
+// call takes no memory beyond its tables; on the host where T is too small for
+// the rows (a 24^3 system of a few orbitals: 0.1 MB).  Laid out on the host the
+// 30 MB of 120^3 with 256 atoms took 15 ms longer.
+static ks_status put_lane_rows(ks_system* s, const ProjHost& ph, const int4* item, const int* lane_off,
+                               unsigned short* lane_pos, double* lane_beta) {
+  const int nwaves = (int)ph.lane_off.size() - 1, np = ph.nproj;
+  const size_t entries = (size_t)ph.lane_off.back() * 64;
+  if (entries == 0) return KS_OK;
+  const size_t es = s->prec == KS_FP64 ? sizeof(double2) : sizeof(float2);
+  const size_t rb = ph.brows.size() * sizeof(double), pb = ph.pt_lds.size() * sizeof(int);
+  if (s->T && rb + pb <= (size_t)s->cb * s->nplanes * s->npl * es) {
+    double* beta = static_cast<double*>(s->T);
+    int* pos = reinterpret_cast<int*>(beta + ph.brows.size());
+    KS_HIP(s, hipMemcpy(beta, ph.brows.data(), rb, hipMemcpyHostToDevice));
+    KS_HIP(s, hipMemcpy(pos, ph.pt_lds.data(), pb, hipMemcpyHostToDevice));
+    launch_lane_rows(nwaves, item, lane_off, pos, beta, np, s->n[0], lane_pos, lane_beta, nullptr);
+    KS_HIP(s, hipGetLastError());
+    KS_HIP(s, hipStreamSynchronize(nullptr));
+    return KS_OK;
+  }
+  std::vector<unsigned short> pos(entries);
+  std::vector<double> beta(entries);
+  for (int w = 0; w < nwaves; ++w)
+    for (int r = ph.lane_off[w], k = 0; r < ph.lane_off[w + 1]; ++r, ++k)
+      for (int l = 0; l < 64; ++l) {
+        const int4 it = ph.item[(size_t)w * 64 + l];
+        const int row = it.x + k;
+        const bool in = row < it.y;
+        pos[(size_t)r * 64 + l] = (unsigned short)(in ? ph.pt_lds[row] : s->n[0]);
+        beta[(size_t)r * 64 + l] = in ? ph.brows[(size_t)row * np + it.z % np] : 0.0;
+      }
+  KS_HIP(s, hipMemcpy(lane_pos, pos.data(), entries * sizeof(unsigned short), hipMemcpyHostToDevice));
+  KS_HIP(s, hipMemcpy(lane_beta, beta.data(), entries * sizeof(double), hipMemcpyHostToDevice));
   return KS_OK;
 }
 
@@ -1165,8 +1238,9 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
       KS_HIP(s, hipMemcpy(*dst, vec.data(), vec.size() * sizeof(T), hipMemcpyHostToDevice));
     return KS_OK;
   };
-  int *pt_lds, *slot_off, *slot_pt, *atom_slot_off, *up_off, *up_key2, *up_x2, *x_slot2;
-  double *brows, *up_beta2, *x_beta2, *kb2;
+  unsigned short* lane_pos = nullptr;
+  int *slot_off, *lane_off, *atom_slot_off, *up_off, *up_key2, *up_x2, *x_slot2;
+  double *lane_beta = nullptr, *up_beta2, *x_beta2, *kb2;
   int4 *item, *slot_desc2;
   void* partial = nullptr;
   double2* DP = nullptr;
@@ -1174,33 +1248,48 @@ static ks_status install_proj(ks_system* s, const ProjHost& ph, int natoms, cons
   const size_t pbytes = (size_t)s->cb * std::max<size_t>(1, ph.slot_atom.size()) * std::max(1, np) * sizeof(double2);
   const size_t dbytes = (size_t)s->cb * std::max(1, na) * std::max(1, np) * sizeof(double2);
   ks_status st;
-  if ((st = put(ph.pt_lds, &pt_lds)) != KS_OK || (st = put(ph.slot_off, &slot_off)) != KS_OK ||
-      (st = put(slot_desc, &slot_desc2)) != KS_OK || (st = put(ph.slot_pt, &slot_pt)) != KS_OK ||
+  if ((st = put(ph.slot_off, &slot_off)) != KS_OK ||
+      (st = put(slot_desc, &slot_desc2)) != KS_OK || (st = put(ph.lane_off, &lane_off)) != KS_OK ||
       (st = put(ph.atom_slot_off, &atom_slot_off)) != KS_OK ||
       (st = put(ph.up_off, &up_off)) != KS_OK || (st = put(up_key, &up_key2)) != KS_OK ||
       (st = put(up_x, &up_x2)) != KS_OK || (st = put(x_slot, &x_slot2)) != KS_OK ||
-      (st = put(ph.brows, &brows)) != KS_OK || (st = put(up_beta, &up_beta2)) != KS_OK ||
+      (st = put(up_beta, &up_beta2)) != KS_OK ||
       (st = put(x_beta, &x_beta2)) != KS_OK || (st = put(kb, &kb2)) != KS_OK || (st = put(ph.item, &item)) != KS_OK ||
       (st = dalloc(s, &partial, pbytes)) != KS_OK ||
       (fresh.push_back(partial), st = dalloc(s, reinterpret_cast<void**>(&DP), dbytes)) != KS_OK) {
     for (void*& q : fresh) dfree(s, q);
     return st;
   }
+  {
+    const size_t entries = (size_t)ph.lane_off.back() * 64;
+    void *lp = nullptr, *lb = nullptr;
+    if ((st = dalloc(s, &lp, entries * sizeof(unsigned short))) == KS_OK) fresh.push_back(lp);
+    if (st == KS_OK && (st = dalloc(s, &lb, entries * sizeof(double))) == KS_OK) fresh.push_back(lb);
+    if (st == KS_OK) {
+      lane_pos = static_cast<unsigned short*>(lp);
+      lane_beta = static_cast<double*>(lb);
+      st = put_lane_rows(s, ph, item, lane_off, lane_pos, lane_beta);
+    }
+    if (st != KS_OK) {
+      for (void*& q : fresh) dfree(s, q);
+      return st;
+    }
+  }
   auto swap_in = [&](auto*& field, auto* v) {
     void* old = field;
     dfree(s, old);
     field = v;
   };
-  swap_in(s->d_pt_lds, pt_lds);
+  swap_in(s->d_lane_pos, lane_pos);
   swap_in(s->d_slot_off, slot_off);
   swap_in(s->d_slot_desc, slot_desc2);
-  swap_in(s->d_slot_pt, slot_pt);
+  swap_in(s->d_lane_off, lane_off);
   swap_in(s->d_atom_slot_off, atom_slot_off);
   swap_in(s->d_up_off, up_off);
   swap_in(s->d_up_key, up_key2);
   swap_in(s->d_up_x, up_x2);
   swap_in(s->d_x_slot, x_slot2);
-  swap_in(s->d_beta, brows);
+  swap_in(s->d_lane_beta, lane_beta);
   swap_in(s->d_up_beta, up_beta2);
   swap_in(s->d_x_beta, x_beta2);
   swap_in(s->d_kb, kb2);

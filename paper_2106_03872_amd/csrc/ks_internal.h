@@ -35,10 +35,8 @@ struct SphereTab {
 //           (the first atom) stored with the point, and the extra entries of
 //           points where spheres overlap, stored apart (scatter side)
 struct ProjTab {
-  const int* pt_lds;         // [npoints] LDS offset of each beta row's point
   const int* slot_off;       // [ntiles+1] slot range of each tile
   const int4* slot_desc;     // [nslots] first and end partial sum of the slot's atom (atom order), atom
-  const int* slot_pt;        // [nslots+1] beta-row range of each slot
   const int* atom_slot_off;  // [natoms+1] partial sums of each atom (partials are ordered by atom, then tile)
   const int* up_off;         // [ntiles+1] unique-point range of each tile
   const int* up_key;         // [nunique] LDS offset | primary slot << 16 | extra entries << 24
@@ -46,9 +44,11 @@ struct ProjTab {
   const double* up_beta;     // [nunique][nproj] beta row of the primary entry
   const int* x_slot;         // [nextra] tile-local slot of each extra entry
   const double* x_beta;      // [nextra][nproj]
-  const double* beta;        // [npoints][nproj], rows in slot order
   const double* d;           // [natoms][nproj]
   const int4* item;          // [ntiles][threads per x-block] projection work of each lane (see build_proj)
+  const int* lane_off;       // [ntiles][waves] (+1) first row of each wave's lanes
+  const unsigned short* lane_pos;   // [rows][64] LDS offset of each lane's row (below NB (n0 + 1) <= 8256)
+  const double* lane_beta;   // [rows][64]
   int natoms, nproj, nslots;
 };
 
@@ -90,6 +90,7 @@ constexpr int KB_MAX_NPROJ = 8;        // projectors per atom
 constexpr size_t GEMM_PART_MAX = 256ull << 20;    // largest split-K partial buffer of the n x n products
 constexpr int KB_TILE_DP = 128;        // (slot, projector) pairs staged per x-tile
 constexpr int KB_CACHED_POINTS = 16;   // points of an item held in registers across orbitals
+constexpr int KB_ROW_GROUP = 4;        // rows of a lane read together
 constexpr int KB_MAX_GROUP_LOG = 4;    // at most 16 lanes per (slot, projector) pair
 // Largest y extent of a launch grid.  The pass kernels put the orbitals of a
 // pass (or their groups, or the rows of a batch) on it, so a pass holds at
@@ -164,10 +165,11 @@ struct ks_system {
   // (real space), 1 = the reciprocal-space split-BF16 product with the table
   // gp (mixed precision; ks_tuning.projection)
   int proj_mode = 0;
-  int *d_pt_lds = nullptr, *d_slot_off = nullptr, *d_slot_pt = nullptr,
+  unsigned short* d_lane_pos = nullptr;
+  int *d_slot_off = nullptr, *d_lane_off = nullptr,
       *d_atom_slot_off = nullptr, *d_up_off = nullptr, *d_up_key = nullptr,
       *d_up_x = nullptr, *d_x_slot = nullptr;
-  double *d_beta = nullptr, *d_up_beta = nullptr, *d_x_beta = nullptr, *d_kb = nullptr;
+  double *d_lane_beta = nullptr, *d_up_beta = nullptr, *d_x_beta = nullptr, *d_kb = nullptr;
   int4 *d_item = nullptr, *d_slot_desc = nullptr;
   long long slot_sq = 0;   // sum over slots of their atom's slot count
   ks::GTab gp;
@@ -280,6 +282,10 @@ bool launch_plane_inv(const ks_system* s, int nb, const void* pk, bool in_fp64, 
 // added (accumulate) to rho
 bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, const double* occ, double* rho,
                   int accumulate, hipStream_t st);
+// Lane-by-lane copies of the projection rows (see build_proj): for every wave's
+// lanes, positions and betas of their rows, n0 and 0 past a lane's last row.
+void launch_lane_rows(int nwaves, const int4* item, const int* lane_off, const int* pt_lds, const double* beta, int np,
+                      int n0, unsigned short* lane_pos, double* lane_beta, hipStream_t st);
 bool launch_proj_reduce(const ks_system* s, int nb, const void* partial, double2* DP, hipStream_t st);
 // partial: the projections are also summed here from xproj's partial sums
 // (xapply_sums says where that pays) instead of read from DP
@@ -414,10 +420,8 @@ inline SphereTab sphere_tab(const ks_system* s) {
 
 inline ProjTab proj_tab(const ks_system* s) {
   ProjTab c;
-  c.pt_lds = s->d_pt_lds;
   c.slot_off = s->d_slot_off;
   c.slot_desc = s->d_slot_desc;
-  c.slot_pt = s->d_slot_pt;
   c.atom_slot_off = s->d_atom_slot_off;
   c.up_off = s->d_up_off;
   c.up_key = s->d_up_key;
@@ -425,9 +429,11 @@ inline ProjTab proj_tab(const ks_system* s) {
   c.up_beta = s->d_up_beta;
   c.x_slot = s->d_x_slot;
   c.x_beta = s->d_x_beta;
-  c.beta = s->d_beta;
   c.d = s->d_kb;
   c.item = s->d_item;
+  c.lane_off = s->d_lane_off;
+  c.lane_pos = s->d_lane_pos;
+  c.lane_beta = s->d_lane_beta;
   c.natoms = s->natoms;
   c.nproj = s->nproj;
   c.nslots = s->nslots;
