@@ -676,13 +676,17 @@ bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, cons
 // Whether the x-apply blocks sum the projections themselves: every slot of a
 // tile then re-reads all partial sums of its atom (`values` in all: orbitals x
 // nproj x the sum over slots of their atom's slot count), at the head of each
-// orbital, against one launch of proj_reduce.  Up to 6 MB the launch costs more:
-// 24^3 / 10 orbitals, 47 KB: xapply 6.3 -> 6.8 us, without a launch of 2.7 us;
-// 48x40^2 / 33, 4 MB: 17.0 -> 18.1 us, without 4.1 us.  Beyond, the reads do: 32^3 /
-// 262 in a batch, 7 MB: 35.8 -> 40.9 us, without 4.8 us; 60^3 / 96, 14 MB: 72 ->
-// 110 us, without 4.8 us.
-bool xapply_sums(const ks_system* s, long long values) {
-  return s->xshape < 2 && values * (long long)(mixed(s) ? sizeof(float2) : sizeof(double2)) <= (6ll << 20);
+// orbital, against one launch of proj_reduce.  The launch costs more while the
+// blocks (a tile of an orbital each) run in at most about two rounds, 2048 of
+// them, and read up to 6 MB: 24^3 / 10 orbitals, 90 blocks, 47 KB: xapply 6.3 ->
+// 6.8 us, without a launch of 2.7 us; 48x40^2 / 33, 1650 blocks, 4 MB: 17.0 ->
+// 18.1 us, without 4.1 us.  Beyond, each round pays the latency of that head, or
+// the reads do: 96^3 / 24, complex64, 6912 blocks, 5 MB: 56 -> 88 us, without 5.7
+// us; 120^3 / 36, complex64, 16200 blocks: 186 -> 228 us; 32^3 / 262 in a batch, 7
+// MB: 35.8 -> 40.9 us, without 4.8 us; 60^3 / 96, 14 MB: 72 -> 110 us.
+bool xapply_sums(const ks_system* s, long long orbitals, long long values) {
+  return s->xshape < 2 && s->ntiles * orbitals <= 2048 &&
+         values * (long long)(mixed(s) ? sizeof(float2) : sizeof(double2)) <= (6ll << 20);
 }
 
 template <int N0, bool HB, bool SUMS>

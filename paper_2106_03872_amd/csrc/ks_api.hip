@@ -582,7 +582,7 @@ ks_status x_passes(ks_system* s, int nb, const void* win, bool win_fp64, hipStre
   } else if (s->natoms > 0) {
     r = kcall(s, KS_K_XPROJ, st, "xproj", [&] { return launch_xproj(s, nb, s->T, s->partial, occ, rho, accumulate, st); });
     if (r != KS_OK) return r;
-    if (xapply_sums(s, s->slot_sq * s->nproj * nb)) {
+    if (xapply_sums(s, nb, s->slot_sq * s->nproj * nb)) {
       sums = s->partial;
     } else {
       r = kcall(s, KS_K_PROJ_REDUCE, st, "proj_reduce", [&] { return launch_proj_reduce(s, nb, s->partial, s->DP, st); });
@@ -2078,7 +2078,7 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
       h.max_natoms = std::max(h.max_natoms, t->sys->natoms);
     }
     h.njobs = (int)js.size();
-    h.sums = xapply_sums(s0, sq);
+    h.sums = xapply_sums(s0, total, sq);
     const int gx = x_group_size(s0, total), gp = plane_group_size(s0, total);
     for (int q = 0; q < h.njobs; ++q) {
       const int nb = nbs[q];

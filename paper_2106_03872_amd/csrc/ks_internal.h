@@ -291,7 +291,7 @@ bool launch_proj_reduce(const ks_system* s, int nb, const void* partial, double2
 // (xapply_sums says where that pays) instead of read from DP
 bool launch_xapply(const ks_system* s, int nb, const void* T, const double2* DP, const void* partial, void* U,
                    hipStream_t st);
-bool xapply_sums(const ks_system* s, long long values);
+bool xapply_sums(const ks_system* s, long long orbitals, long long values);
 // next (where plane_next says so): also the plane synthesis into T, 1 of the
 // H psi formed (wout), 2 of the accumulated state
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
