@@ -2328,6 +2328,35 @@ ks_status ks_propagate_batch(ks_state* const* states, int nstates, double dt, in
   return r;
 }
 
+// Bytes of the projection tables (install_proj) of npoints points of np
+// projectors, the most over the tile shapes of the grid.  The lanes of a wave
+// are laid out with the row count of its longest: at most KB_CACHED_POINTS while
+// a tile's lanes suffice for that, and the waves with rows are then one per
+// tile with points and one per 64 lanes (a lane per pair, doubled at most until
+// a lane has KB_CACHED_POINTS).  Where lanes are too few or groups at their
+// limit, the layout grows with the points: measured on the host for random
+// spheres of one radius and of radii 3.5 to 9 grid spacings, up to the densest
+// that a tile takes, it then has at most 1.97 entries per point and projector.  As
+// for the partials, a slot is taken to have at least eight points.
+static double proj_table_bytes(const int n[3], double npoints, double np) {
+  if (npoints <= 0.0) return 0.0;
+  const double slots = npoints / 8.0;
+  double most = 0.0;
+  for (int shape = 0; shape < 4; ++shape) {
+    if (!x_shape_available(n[0], shape)) continue;
+    const int nb = x_shape_nb(n[0], shape), nt = x_shape_threads(shape);
+    const double tiles = (double)(((long long)n[1] * n[2] + nb - 1) / nb), waves = tiles * (nt / 64);
+    const double lanes = np * (slots + npoints / 8.0);
+    const double rows = KB_CACHED_POINTS * std::min(waves, std::min(tiles, slots) + lanes / 64.0);
+    const double entries = std::max(64.0 * rows, 2.5 * np * npoints);
+    const double b = entries * (sizeof(unsigned short) + sizeof(double)) + tiles * nt * sizeof(int4)   // lanes, items
+                     + (waves + 2.0 * tiles + 3.0) * sizeof(int);                                      // ranges
+    most = std::max(most, b);
+  }
+  return most + npoints * (np * 8.0 + 8.0)            // scatter rows: beta, key and extra entries (or slot)
+         + slots * (sizeof(int4) + 4.0 + np * 8.0);   // slot descriptors; per atom (at most one per slot)
+}
+
 ks_status ks_plan_footprint(const int n[3], const double L[3], double ecut, int precision, int norb, int npoints,
                             int nproj, int chunk, unsigned long long* bytes) {
   if (!n || !L || !bytes || norb < 1 || npoints < 0) return fail(nullptr, KS_EINVAL, "bad argument");
@@ -2349,7 +2378,7 @@ ks_status ks_plan_footprint(const int n[3], const double L[3], double ecut, int 
   b += N * 40.0 + 2.0 * norb * 8.0;                     // potential, static potential, density and complex
                                                         // work box of the Hartree solve; reductions
   b += (double)((cb + 7) / 8) * N * 8.0;                // partial densities
-  b += npoints * (np * 8.0 + 4 * 4.0) + 64.0 * 1024;    // KB tables
+  b += proj_table_bytes(n, npoints, np) + 64.0 * 1024;  // projection tables; small tables and alignment
   b += (double)cb * npoints * np * 16.0 / 8.0;          // projection partials (upper bound)
   b += (double)norb * stride * 16.0;                    // resident state
   b += 2.0 * norb * norb * 16.0 + (double)gemm_part_bytes(norb, h.npw);   // orthonormalisation
