@@ -132,14 +132,31 @@ bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4
   }
 }
 
-// Whether the plane analysis goes on to the next synthesis: wherever
-// the coefficients of the G orbitals' plane fit the y-batch's LDS, which is
-// free by then.  It paid at every size and launch measured (see the kernel);
-// larger planes (wide spheres past 120) keep the two launches.
-bool plane_next(const ks_system* s) {
+// Whether the plane analyses of a launch over `orbitals` go on to the next
+// synthesis (the results are the same, bit for bit).
+// - The coefficients of the G orbitals' plane have to fit the y-batch's LDS,
+//   which is free by then.  They do not on spheres wide for their plane: with
+//   E_cut = 10 Ha from a spacing of 0.30 bohr on at 128 points, 0.36 at 120
+//   in complex64, 0.48 at 72 in FP64, 0.58 at 40 and 96 in complex64, 48 and
+//   60 in FP64, 64 and 80 in both.
+// - In FP64 at 60, 72 and 80 points the synthesis runs slower in the analysis's
+//   work split than in its own, by more than a launch once the launch has over
+//   about eight blocks per compute unit.  Steps of 4 H psi, two launches against
+//   one, default group caps, us: 60^3 / 64 orbitals (1792 blocks) 706 and 697, /
+//   96 (2688) 968 and 981, / 160 1531 and 1559; 72^3 / 48 (1584) 877 and 865, /
+//   192 (6336) 2928 and 2970; 80^3 / 32 (1184) 775 and 773, / 48 (1776) 1054 and
+//   1068, / 192 (7104) 3649 and 3704.
+// Elsewhere one launch was faster or within the spread (see the kernel), but for
+// 96 points in FP64 between 64 and 128 orbitals (2051 and 2067 us / 64, 3003 and
+// 3072 / 96, 3889 and 3924 / 128; 1164 and 1144 / 32, 15258 and 15111 / 512), 40
+// in complex64 at 512 (945 and 963) and 120 in complex64 at 96 (4522 and 4578;
+// 22589 and 22098 / 512): no line between sizes or launches separates those.
+bool plane_next(const ks_system* s, long long orbitals) {
+  const int n = s->n[1];
+  if (!mixed(s) && (n == 60 || n == 72 || n == 80) && s->nplanes * orbitals > 2048) return false;
   bool fits = false;
   with_plane_cfg<true>(s, [&](auto c) {
-    fits = (size_t)decltype(c)::G * s->npp_max <= (size_t)decltype(c)::YB * (s->n[1] + 1);
+    fits = (size_t)decltype(c)::G * s->npp_max <= (size_t)decltype(c)::YB * (n + 1);
   });
   return fits;
 }

@@ -651,7 +651,7 @@ ks_status taylor_packed(ks_system* s, int nb, double2* state, double dt, int nst
   taylor_coefficients(dt, coef);
   ks_status r;
   const bool fuse = rho && s->natoms > 0;
-  const bool chain = plane_next(s);   // plane analyses go on to the next synthesis
+  const bool chain = plane_next(s, nb);   // plane analyses go on to the next synthesis
   for (int step = 0; step < nsteps; ++step) {
     // w1 = H psi -> pk1, w2 -> pk2, w3 -> pk1, w4 not stored; state += a_k w_k
     void* src[4] = {state, s->pk[1], s->pk[2], s->pk[1]};
@@ -732,7 +732,7 @@ ks_status etrs_packed(ks_system* s, ks_state* t, double dt, int nsteps, const do
       for (int k = 1; k <= 4; ++k) {
         Taylor tay{ch[k], k < 4 ? 1 : 0, cf[k]};
         const bool in64 = k == 1 || s->prec == KS_FP64;
-        const bool chain = plane_next(s);
+        const bool chain = plane_next(s, nb);
         if ((r = hpsi_packed(s, nb, src[k - 1], in64, dst[k - 1], slice, H_TAYLOR, tay, st, nullptr, nullptr, 0, pred,
                              Chain{chain && k > 1, chain && k < 4 ? 1 : 0})) != KS_OK)
           return r;
@@ -2058,7 +2058,7 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
     std::vector<BatchJob> jobs;
     std::vector<int4> rx, rp, rr;
     int njobs = 0, max_natoms = 0;
-    bool sums = false;
+    bool sums = false, chain = false;
   };
   std::vector<Host> hp(npass);
   size_t total_bytes = 0;
@@ -2079,6 +2079,7 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
     }
     h.njobs = (int)js.size();
     h.sums = xapply_sums(s0, total, sq);
+    h.chain = plane_next(s0, total);
     const int gx = x_group_size(s0, total), gp = plane_group_size(s0, total);
     for (int q = 0; q < h.njobs; ++q) {
       const int nb = nbs[q];
@@ -2150,6 +2151,7 @@ ks_status ks_batch_create(ks_state* const* states, int nstates, ks_batch** out) 
     bp.nrows_r = (int)h.rr.size();
     bp.max_natoms = h.max_natoms;
     bp.sums = h.sums;
+    bp.chain = h.chain;
   }
   const hipError_t e = hipMemcpy(b->dev, host.data(), b->dev_bytes, hipMemcpyHostToDevice);
   if (e != hipSuccess) {
@@ -2204,14 +2206,13 @@ static ks_status batch_taylor(ks_batch* b, double dt, int nsteps, hipStream_t st
   taylor_coefficients(dt, coef);
   ks_status r;
   // chunk-outer, step-inner, as a state stepped alone
-  const bool chain = plane_next(s0);   // plane analyses go on to the next synthesis
   for (const ks_batch_pass& bp : b->passes) {
     for (int step = 0; step < nsteps; ++step) {
       for (int k = 1; k <= 4; ++k) {
         const BatchJob* jobs = bp.jobs[k - 1];
         const bool in64 = k == 1 || s0->prec == KS_FP64;
         const Taylor tay{coef[k], k < 4 ? 1 : 0, {0.0, 0.0}};
-        if (!(chain && (k > 1 || step > 0)) &&
+        if (!(bp.chain && (k > 1 || step > 0)) &&
             (r = kcall(s0, KS_K_PLANE_INV, st, "plane_inv",
                        [&] {
                          return row_slices(bp.rows_p, bp.nrows_p, [&](const int4* rs, int n) {
@@ -2244,7 +2245,7 @@ static ks_status batch_taylor(ks_batch* b, double dt, int nsteps, hipStream_t st
         if ((r = kcall(s0, KS_K_PLANE_FWD, st, "plane_fwd",
                        [&] {
                          return row_slices(bp.rows_p, bp.nrows_p, [&](const int4* rs, int n) {
-                           const int next = !chain ? 0 : k < 4 ? 1 : step < nsteps - 1 ? 2 : 0;
+                           const int next = !bp.chain ? 0 : k < 4 ? 1 : step < nsteps - 1 ? 2 : 0;
                            return launch_plane_fwd_batch(s0, jobs, rs, n, in64, tay, next, st);
                          });
                        })) !=

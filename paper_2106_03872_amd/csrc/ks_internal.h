@@ -255,6 +255,7 @@ struct ks_batch_pass {
   int4* rows_r = nullptr;                 // projection-reduce rows (job, orbital)
   int nrows_x = 0, nrows_p = 0, nrows_r = 0, max_natoms = 0;
   bool sums = false;                      // projections summed in the x-apply pass (no proj_reduce)
+  bool chain = false;                     // plane analyses go on to the next synthesis (plane_next)
 };
 
 // Several resident states of distinct systems of one grid, stepped together
@@ -296,7 +297,7 @@ bool xapply_sums(const ks_system* s, long long orbitals, long long values);
 // H psi formed (wout), 2 of the accumulated state
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
                       void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, hipStream_t st);
-bool plane_next(const ks_system* s);
+bool plane_next(const ks_system* s, long long orbitals);
 // the same from and to boxes (complex128 [n0][n1][n2] per orbital, the result zero outside the sphere)
 bool launch_plane_inv_box(const ks_system* s, int nb, const double2* box, void* T, hipStream_t st);
 bool launch_plane_fwd_box(const ks_system* s, int nb, const void* U, const double2* in, double2* out, hipStream_t st);

@@ -273,7 +273,8 @@ __global__ __launch_bounds__((pcfg<N, R, false>::NT)) __attribute__((amdgpu_wave
 // the start of a block (tables, twiddles): a step of 4 H psi measured 506 -> 451
 // us (24^3, 10 orbitals, mixed), 1480 -> 1435 (60^3, 96, mixed), 2585 -> 2531
 // (64^3, 128, FP64), 34.5 -> 33.7 ms (96^3, 512, FP64), 53.0 -> 51.1 ms (120^3,
-// 1024, mixed).
+// 1024, mixed).  The synthesis then runs in the analysis's work split;
+// plane_next says for which sizes and launches.
 //
 // BOX: input and result are boxes [n0][N][N] (win, acc; the result alone, no
 // mode).  The epilogue goes over all points of the plane, zero outside the
