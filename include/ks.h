@@ -553,8 +553,9 @@ typedef struct {
                         ks_autotune does not change it; -1 in ks_system_set_tuning keeps it */
 } ks_tuning;
 
-/* Time one H psi pass over min(norb, chunk) orbitals (zero coefficients; the
- * kernels' timing does not depend on the values) for each candidate of
+/* Time one H psi pass over min(norb, chunk) orbitals, in the form that a
+ * Taylor step's inner ones have (zero coefficients; the kernels' timing does
+ * not depend on the values), for each candidate of
  * x-pass shape (tile and radix plan) and group caps on `stream`, keep the
  * fastest (a shape later in the order 0..3 only when it is at least 1 % faster
  * than the best earlier one, so that near-ties do not flip between runs), and

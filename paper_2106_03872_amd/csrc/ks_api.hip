@@ -2465,9 +2465,20 @@ ks_status ks_autotune(ks_system* s, int norb, void* stream, ks_tuning* out) {
   };
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     return done(fail(s, KS_EDEVICE, "hipEventCreate failed"));
-  if (hipMemsetAsync(s->pk[0], 0, (size_t)nb * s->npw_stride * sizeof(double2), st) != hipSuccess)
+  if (hipMemsetAsync(s->pk[0], 0, (size_t)nb * s->npw_stride * sizeof(double2), st) != hipSuccess ||
+      hipMemsetAsync(s->pk[1], 0, (size_t)nb * s->npw_stride * (s->prec == KS_FP64 ? sizeof(double2) : sizeof(float2)),
+                     st) != hipSuccess)
     return done(fail(s, KS_EDEVICE, "hipMemsetAsync failed"));
-  Taylor none{{0.0, 0.0}, 0, {0.0, 0.0}};
+  // H psi as three of a step's four take it: from the working precision with
+  // the Taylor sum, and where plane_next says so with the synthesis of the next
+  // in the analysis.  (Timed as a synthesis and an analysis without it, the
+  // plane group was chosen for launches that a step does not make.)
+  const Taylor tay{{0.0, 0.0}, 1, {0.0, 0.0}};
+  const bool chain = plane_next(s, nb);
+  const auto one_hpsi = [&](bool have_t) {
+    return hpsi_packed(s, nb, s->pk[1], s->prec == KS_FP64, s->pk[2], s->pk[0], H_TAYLOR, tay, st, nullptr, nullptr, 0,
+                       nullptr, Chain{have_t, chain ? 1 : 0});
+  };
   const int xgs[] = {2, 4, 8, 16, 32, 64};
   const int pgs[] = {1, 2, 4, 8, 16};
   // Within a shape the fastest caps win; a later shape (in the order 0..3)
@@ -2485,10 +2496,10 @@ ks_status ks_autotune(ks_system* s, int norb, void* stream, ks_tuning* out) {
       for (int pg : pgs) {
         s->xg_max = xg;
         s->pg_max = pg;
-        if ((r = hpsi_packed(s, nb, s->pk[0], true, s->pk[1], nullptr, H_OUT, none, st)) != KS_OK) return done(r);
+        if ((r = one_hpsi(false)) != KS_OK) return done(r);
         if (hipEventRecord(e0, st) != hipSuccess) return done(fail(s, KS_EDEVICE, "hipEventRecord failed"));
         for (int rep = 0; rep < 2; ++rep)
-          if ((r = hpsi_packed(s, nb, s->pk[0], true, s->pk[1], nullptr, H_OUT, none, st)) != KS_OK) return done(r);
+          if ((r = one_hpsi(chain)) != KS_OK) return done(r);
         if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
           return done(fail(s, KS_EDEVICE, "event timing failed"));
         float ms = 0.0f;
