@@ -3,14 +3,20 @@
 
 namespace ks {
 
-// The bound a sphere has to keep to be accepted: one plane's columns, a batch
-// of 64 (n1 <= 64), 48, 24 or 16 rows and one byte per packed coefficient of
-// the plane within the 160 KB of a compute unit.  The passes use no more.
+// The LDS that a sphere must leave within the 160 KB of a compute unit to be
+// accepted: one plane's columns, a batch of 64 (n1 <= 64), 48, 24 or 16 rows
+// and one byte per packed coefficient of the plane; and what the passes are
+// launched with, which is more than that in some sizes (their largest splits,
+// and the column tables beside the dynamic part).  Over the numbers of columns
+// that a sphere can have, odd or the whole plane, no sphere that keeps the
+// former exceeds 160 KB in the latter: it stands here for rows to come.
 size_t plane_lds_bytes(const ks_system* s) {
   const int N = s->n[1];
   const int yb = N <= 64 ? 64 : (N <= 96 ? 48 : (N <= 120 ? 24 : 16));
   const size_t es = s->prec == KS_FP64 ? sizeof(double2) : sizeof(float2);
-  return es * ((size_t)N + (size_t)s->ncol_max * (N + 1) + (size_t)yb * (N + 1)) + ((size_t)s->npp_max + 15) / 16 * 16;
+  const size_t bound =
+      es * ((size_t)N + (size_t)s->ncol_max * (N + 1) + (size_t)yb * (N + 1)) + ((size_t)s->npp_max + 15) / 16 * 16;
+  return std::max(bound, std::max(plane_smem<false>(s), plane_smem<true>(s)) + PLANE_TABLES);
 }
 
 // Orbitals per plane block for a launch over `total` orbitals: up to pg_max,

@@ -501,7 +501,9 @@ void with_plane_cfg(const ks_system* s, F&& f) {
   }
 }
 
-// LDS of a plane block (dynamic part)
+// LDS of a plane block: the dynamic part, and the column tables s_off and
+// s_m2lo that the kernels declare
+constexpr size_t PLANE_TABLES = (130 + 129) * sizeof(int);
 template <bool FWD>
 size_t plane_smem(const ks_system* s) {
   size_t rows = 0;
