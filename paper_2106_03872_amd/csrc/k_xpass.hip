@@ -486,9 +486,11 @@ __global__ __launch_bounds__(SH::XT) void xapply_kernel(const cplx<R>* __restric
 // straight from the last synthesis stage over the group's orbitals in order
 // and written to the group's partial density; dens_sum adds the groups in
 // order.
-// (The band-limited FP64 form is held to the 168 registers of three waves per SIMD.)
+// (The band-limited FP64 form is held to the 168 registers of three waves per
+// SIMD up to 96 points: 32 x 256 tiles of 96 spill two registers for it.  Beyond,
+// two blocks of that tile fill the LDS of a compute unit.)
 template <int N0, class SH, typename R, bool HB>
-__global__ __launch_bounds__(SH::XT) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && HB ? 3 : 1))) void xdens_kernel(const cplx<R>* __restrict__ Tin, int nb,
+__global__ __launch_bounds__(SH::XT) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && HB && N0 <= 96 ? 3 : 1))) void xdens_kernel(const cplx<R>* __restrict__ Tin, int nb,
                                                    const double* __restrict__ occ, double* __restrict__ part,
                                                    SphereTab tab, const cplx<R>* __restrict__ tw0,
                                                    double inv_omega) {
