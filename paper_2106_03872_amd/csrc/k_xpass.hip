@@ -613,9 +613,14 @@ int x_shape_threads(int shape) { return shape == 1 || shape == 3 ? 192 : NT; }
 // densities, which dens_sum adds in order: groups of at least DENS_GROUP
 // orbitals, at most `most` of them.  A launch that leaves more than half of the
 // compute units' block slots empty that way (fewer than 512 blocks: small
-// grids, few orbitals) takes more and smaller groups, as many as U, which is
-// written only after a density pass, holds (24^3, 10 orbitals, complex64: the
-// projections with the density took 14.9 us in 2 groups, 11.4 in 5).
+// grids, few orbitals) takes more and smaller groups, up to that number of blocks
+// and as far as U, which is written only after a density pass, holds them.  A
+// block's orbitals and the sum over groups are two chains, so the shortest are
+// groups of about sqrt(nb) / 1.5 orbitals: a density pass of 24^3 with its
+// synthesis took, in 1, 2, 3, 5, 8, 12, 24 groups, 30, 22, 19, 17.7, 17.7, 17.6,
+// 20.6 us (24 orbitals, FP64); of 12 x 8 x 8 in 8, 12, 20, 32, 64, 128 groups 29, 26,
+// 23, 23, 30, 45 us (160 orbitals); one group per orbital took twice the time of
+// groups of 8 there.
 struct DensPlan {
   int ng;
   double* part;
@@ -623,9 +628,11 @@ struct DensPlan {
 static DensPlan dens_plan(const ks_system* s, int nb, int most) {
   const int by_size = std::max(1, std::min(most, (nb + DENS_GROUP - 1) / DENS_GROUP));
   const int by_fill = (512 + s->ntiles - 1) / s->ntiles;
+  const int orbitals = std::max(1, (int)lround(sqrt((double)nb) / 1.5));
+  const int by_chain = (nb + orbitals - 1) / orbitals;
   const size_t es = mixed(s) ? sizeof(float2) : sizeof(double2);
   const size_t fit = (size_t)s->cb * s->nplanes * es / ((size_t)s->n[0] * sizeof(double));
-  const int ng = (int)std::min<size_t>(fit, std::min(nb, std::min(most, by_fill)));
+  const int ng = (int)std::min<size_t>(fit, std::min({by_chain, most, by_fill}));
   if (ng > by_size) return {ng, static_cast<double*>(s->U)};
   return {by_size, s->dens_part};
 }
