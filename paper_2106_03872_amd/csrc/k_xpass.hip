@@ -686,18 +686,37 @@ bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, cons
 // Whether the x-apply blocks sum the projections themselves: every slot of a
 // tile then re-reads all partial sums of its atom (`values` in all: orbitals x
 // nproj x the sum over slots of their atom's slot count), at the head of each
-// orbital, against one launch of proj_reduce.  The launch costs more while the
-// blocks (a tile of an orbital each) run in at most about two rounds, 2048 of
-// them, and read up to 6 MB: 24^3 / 10 orbitals, 90 blocks, 47 KB: xapply 6.3 ->
-// 6.8 us, without a launch of 2.7 us; 48x40^2 / 33, 1650 blocks, 4 MB: 17.0 ->
-// 18.1 us, without 4.1 us.  Beyond, each round pays the latency of that head, or
-// the reads do: 96^3 / 24, complex64, 6912 blocks, 5 MB: 56 -> 88 us, without 5.7
-// us; 120^3 / 36, complex64, 16200 blocks: 186 -> 228 us; 32^3 / 262 in a batch, 7
-// MB: 35.8 -> 40.9 us, without 4.8 us; 60^3 / 96, 14 MB: 72 -> 110 us.
+// orbital, against one launch of proj_reduce.  Measured per step of 4 H psi,
+// launch against head, 2 to 128 orbitals with atoms at one per 3000, 9000 and
+// 20000 points:
+// - 64-pencil tiles (n0 <= 32): 5 to 9 us less up to 1152 blocks, 1 to 3 at 2048
+//   (blocks: a tile of an orbital each);
+// - 32-pencil tiles in FP64: 4 to 8 us less while the blocks are resident at
+//   once, four per compute unit at 40, 48 and 64 points (64^3 / 8, 1024: 146.6 and
+//   140.2 us) and three elsewhere (72^3 / 4, 648: 165 and 160), and still 1 to 5
+//   at 40 and 48 points up to 1792 (48^3 / 24, 1728: 173 and 169).  Beyond, each
+//   further round pays the head's latency: 60^3 / 8, 904: 168 and 184; 72^3 / 16,
+//   2592: 388 and 400; 96^3 / 8, 2304: 400 and 405.  On spheres past the band it
+//   is three per compute unit at any size (32^3 / 64, 1024: 186 and 194);
+// - 32-pencil tiles in complex64: slower at every size in the band, by 1 us for
+//   a few orbitals (64^3 / 2, 256: 98 and 102) and by 5 to 40 beyond one round
+//   (40^3 / 24, 1200: 129 and 142; 96^3 / 8, 2304: 276 and 321), so never.
+// And up to 6 MB of reads: 32^3 / 262 in a batch, 7 MB: 35.8 -> 40.9 us for the
+// kernel, without 4.8 us; 60^3 / 96, 14 MB: 72 -> 110 us.
 bool xapply_sums(const ks_system* s, long long orbitals, long long values) {
-  return s->xshape < 2 && s->ntiles * orbitals <= 2048 &&
+  const int n0 = s->n[0];
+  if (s->xshape != 0 || (n0 > 32 && mixed(s))) return false;
+  long long blocks = 768;
+  if (n0 <= 32 && (mixed(s) || s->x_half)) blocks = 2048;
+  else if (s->x_half && n0 <= 48) blocks = 1792;
+  else if (s->x_half && n0 == 64) blocks = 1024;
+  return s->ntiles * orbitals <= blocks &&
          values * (long long)(mixed(s) ? sizeof(float2) : sizeof(double2)) <= (6ll << 20);
 }
+
+// the kernels that exist with the sums: the first tile shape, complex64 up to 32 points
+template <int N0, class SH, typename R>
+constexpr bool has_sums = SH::XT == NT && SH::V == 0 && (N0 <= 32 || sizeof(R) == 8);
 
 template <int N0, bool HB, bool SUMS>
 static void xapply_n(const ks_system* s, int nb, const void* T, const double2* DP, const void* partial, void* U,
@@ -708,14 +727,13 @@ static void xapply_n(const ks_system* s, int nb, const void* T, const double2* D
   const int ng = x_groups(s, nb);
   with_shape<N0>(s, [&](auto sh) {
     using SH = decltype(sh);
-    constexpr bool S = SUMS && SH::V == 0;
     const dim3 grid(s->ntiles, ng);
     if (!mixed(s))
-      xapply_kernel<N0, SH, double, HB, S><<<grid, SH::XT, 0, st>>>((const double2*)T, nb, (double2*)U, s->d_v, DP,
+      xapply_kernel<N0, SH, double, HB, SUMS && has_sums<N0, SH, double>><<<grid, SH::XT, 0, st>>>((const double2*)T, nb, (double2*)U, s->d_v, DP,
                                                                    (const double2*)partial, sc_p, sphere_tab(s),
                                                                    proj_tab(s), s->d_tw0, sc_v);
     else
-      xapply_kernel<N0, SH, float, HB, S><<<grid, SH::XT, 0, st>>>((const float2*)T, nb, (float2*)U, s->d_v, DP,
+      xapply_kernel<N0, SH, float, HB, SUMS && has_sums<N0, SH, float>><<<grid, SH::XT, 0, st>>>((const float2*)T, nb, (float2*)U, s->d_v, DP,
                                                                   (const float2*)partial, sc_p, sphere_tab(s),
                                                                   proj_tab(s), s->d_tw0f, sc_v);
   });
@@ -748,7 +766,6 @@ static void x_batch_n(const ks_system* s, const BatchJob* jobs, const int4* rows
   const double sc_v = 1.0 / (double)s->N, sc_p = sqrt(s->omega) / (double)s->N;
   with_shape<N0>(s, [&](auto sh) {
     using SH = decltype(sh);
-    constexpr bool S = SH::V == 0;
     if (!apply) {
       if (!mixed(s))
         xproj_kernel<N0, SH, double, HB, false, true><<<grid, SH::XT, 0, st>>>(
@@ -757,11 +774,11 @@ static void x_batch_n(const ks_system* s, const BatchJob* jobs, const int4* rows
         xproj_kernel<N0, SH, float, HB, false, true><<<grid, SH::XT, 0, st>>>(
             nullptr, 0, nullptr, sphere_tab(s), ProjTab{}, s->d_tw0f, scale, nullptr, nullptr, 0.0, jobs, rows);
     } else if (!mixed(s)) {
-      auto* k = sums ? xapply_kernel<N0, SH, double, HB, S, true> : xapply_kernel<N0, SH, double, HB, false, true>;
+      auto* k = sums ? xapply_kernel<N0, SH, double, HB, has_sums<N0, SH, double>, true> : xapply_kernel<N0, SH, double, HB, false, true>;
       k<<<grid, SH::XT, 0, st>>>(nullptr, 0, nullptr, nullptr, nullptr, nullptr, sc_p, sphere_tab(s), ProjTab{},
                                  s->d_tw0, sc_v, jobs, rows);
     } else {
-      auto* k = sums ? xapply_kernel<N0, SH, float, HB, S, true> : xapply_kernel<N0, SH, float, HB, false, true>;
+      auto* k = sums ? xapply_kernel<N0, SH, float, HB, has_sums<N0, SH, float>, true> : xapply_kernel<N0, SH, float, HB, false, true>;
       k<<<grid, SH::XT, 0, st>>>(nullptr, 0, nullptr, nullptr, nullptr, nullptr, sc_p, sphere_tab(s), ProjTab{},
                                  s->d_tw0f, sc_v, jobs, rows);
     }
