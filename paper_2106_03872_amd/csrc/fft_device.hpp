@@ -453,6 +453,7 @@ struct first_stage_regs<N, NB, NT, T, radix_list<R, Rest...>, HALF> {
   static_assert(!HALF || R % 4 == 0, "band-limited input needs a first radix divisible by 4");
   static constexpr int radix = R;
   static constexpr int nb = NB, nt = NT;
+  static constexpr bool half = HALF;
   static constexpr int NBF = N / R;
   static constexpr int TOT = NB * NBF;
   static constexpr int items = (TOT + NT - 1) / NT;
