@@ -52,7 +52,7 @@ struct TPos {
 // sphere's planes at a spacing of 0.42 bohr, and their loads, though they only
 // return zeros, take issue slots; a branch skips them: the density pass of 160
 // orbitals in complex64 took 103 us at 80^3 before buffer access, 127 with it
-// and 111 with the branch.
+// and 106 with the branch.
 template <class FR, int N0, typename C>
 __device__ __forceinline__ void load_inputs(FR& r, const TPos<N0, C>& pos, const C* T, unsigned bytes) {
   const gbuf b = make_gbuf(T, bytes);
@@ -121,19 +121,27 @@ __global__ __launch_bounds__(SH::XT) void xproj_kernel(const cplx<R>* __restrict
   }
   const int npl = tab.n1 * tab.n2;
   const int p0 = tile * NB;
-  // the first orbital's loads are issued before the block's tables are read
+  // the block's first loads, independent of each other, are issued together:
+  // the first orbital, the work item, the slot range, the twiddles
   const TPos<N0, C> pos(tab, p0);
   const unsigned tbytes = pos.bytes();
   const long long tstride = (long long)tab.nplanes * npl;
   FR pre;
   if (oa < ob) load_inputs(pre, pos, Tin + oa * tstride, tbytes);
+  const int wave = __builtin_amdgcn_readfirstlane(tile * (XT / 64) + tid / 64);
+  int4 item;
+  int row0, nrow;   // this wave's rows
+  auto read_item = [&] {
+    item = pt.item[(long long)tile * XT + tid];
+    row0 = pt.lane_off[wave];
+    nrow = pt.lane_off[wave + 1] - row0;
+  };
+  if constexpr (!BATCH) read_item();
   const int sA = pt.slot_off[tile], ns = pt.slot_off[tile + 1] - sA;
   if (!DENS && ns == 0) return;  // no sphere point in this tile (uniform per block)
-  // A system whose projectors were never set has slot_off alone of the tables
-  // read here, so the others are read after the return.
-  const int4 item = pt.item[(long long)tile * XT + tid];
-  const int wave = __builtin_amdgcn_readfirstlane(tile * (XT / 64) + tid / 64);
-  const int row0 = pt.lane_off[wave], nrow = pt.lane_off[wave + 1] - row0;   // this wave's rows
+  // A batch runs over all its systems, and one whose projectors were never set
+  // has slot_off alone of these tables: the others are read after the return.
+  if constexpr (BATCH) read_item();
   stage_twiddles<N0, XT, SH::V>(tw, tw0);
   double a[DENS ? LS::items : 1][DENS ? LS::radix : 1];
   if constexpr (DENS) {
