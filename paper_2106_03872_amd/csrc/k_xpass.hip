@@ -719,7 +719,7 @@ bool launch_xproj(const ks_system* s, int nb, const void* T, void* partial, cons
 //   at 40 and 48 points up to 1792 (48^3 / 24, 1728: 173 and 169).  Beyond, each
 //   further round pays the head's latency: 60^3 / 8, 904: 168 and 184; 72^3 / 16,
 //   2592: 388 and 400; 96^3 / 8, 2304: 400 and 405.  On spheres past the band it
-//   is three per compute unit at any size (32^3 / 64, 1024: 186 and 194);
+//   is three per compute unit from 32 points on (32^3 / 64, 1024: 186 and 194);
 // - 32-pencil tiles in complex64: slower at every size in the band, by 1 us for
 //   a few orbitals (64^3 / 2, 256: 98 and 102) and by 5 to 40 beyond one round
 //   (40^3 / 24, 1200: 129 and 142; 96^3 / 8, 2304: 276 and 321), so never.
@@ -729,7 +729,7 @@ bool xapply_sums(const ks_system* s, long long orbitals, long long values) {
   const int n0 = s->n[0];
   if (s->xshape != 0 || (n0 > 32 && mixed(s))) return false;
   long long blocks = 768;
-  if (n0 <= 32 && (mixed(s) || s->x_half)) blocks = 2048;
+  if (n0 <= 24 || (n0 == 32 && (mixed(s) || s->x_half))) blocks = 2048;
   else if (s->x_half && n0 <= 48) blocks = 1792;
   else if (s->x_half && n0 == 64) blocks = 1024;
   return s->ntiles * orbitals <= blocks &&

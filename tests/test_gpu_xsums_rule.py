@@ -39,7 +39,7 @@ def _apply(s, c):
 
 def _limit(n0, half, precision):
     if n0 <= 32:
-        return 2048 if precision or half else 768
+        return 2048 if n0 < 32 or precision or half else 768
     if precision:
         return 0
     return (1792 if n0 <= 48 else 1024 if n0 == 64 else 768) if half else 768
