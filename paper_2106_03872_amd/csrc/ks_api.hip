@@ -1510,6 +1510,20 @@ ks_status ks_propagate_step(ks_system* s, int norb, void* psi, double dt, int ns
   return KS_OK;
 }
 
+// Whether the density of boxes packs them first.  The synthesis that reads the
+// box takes a column per lane, 16 bytes from each row of the plane, where packing
+// reads whole runs.  In complex64 at 64 to 120 points that costs more than the
+// packed copy in launches of more than about 24 blocks per compute unit, whose
+// boxes outgrow the last cache (from the box and packed, us: 72^3 / 160 orbitals,
+// 5280 blocks, 149 and 152, / 240 213 and 202, / 480 441 and 371; 64 x 96^2 / 160,
+// 4640, 185 and 198, / 240, 6960, 289 and 280; past the band 64^3 / 80, 3120, 86
+// and 95, / 160, 6240, 184 and 173; 40 x 120^2 / 400, 6800, 576 from the box, / 160,
+// 2720, faster from it).  In FP64 and at other sizes the box is read (64^3 FP64 /
+// 480 362 and 388; 48^3 complex64 / 480 109 and 123).
+static bool density_packs(const ks_system* s, int nb) {
+  return s->prec == KS_MIXED && s->n[1] >= 64 && s->n[1] <= 120 && (long long)s->nplanes * nb > 6144;
+}
+
 ks_status ks_density(ks_system* s, int norb, const void* psi, const double* occ, double* rho, void* stream) {
   ks_status r = check_common(s, norb);
   if (r != KS_OK) return r;
@@ -1525,6 +1539,12 @@ ks_status ks_density(ks_system* s, int norb, const void* psi, const double* occ,
   for (int o0 = 0; o0 < norb; o0 += cl) {
     const int nb = std::min(cl, norb - o0);
     const double2* box = (const double2*)psi + (size_t)o0 * s->N;
+    if (density_packs(s, nb)) {
+      if ((r = kcall(s, KS_K_PACK, st, "pack", [&] { return launch_pack(s, nb, box, s->N, s->pk[0], st); })) != KS_OK ||
+          (r = density_packed(s, nb, s->pk[0], occ + o0, rho, o0 > 0, st)) != KS_OK)
+        return r;
+      continue;
+    }
     if ((r = kcall(s, KS_K_PLANE_INV, st, "plane_inv", [&] { return launch_plane_inv_box(s, nb, box, s->T, st); })) !=
             KS_OK ||
         (r = density_packed(s, nb, nullptr, occ + o0, rho, o0 > 0, st, true)) != KS_OK)
