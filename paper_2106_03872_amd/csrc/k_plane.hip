@@ -41,28 +41,30 @@ struct BatchRef {
   int nrows = 0;
 };
 
-template <int N, typename R, typename TIN, bool B>
+template <int N, typename R, typename TIN, bool HB, bool B>
 static void plane_inv_t(const ks_system* s, int nb, const void* pk, void* T, const void* tw, const BatchRef& b,
                         hipStream_t st) {
-  using PC = pcfg<N, R, false>;
+  using PC = pcfg<N, R, false, HB>;
   const int stage = PC::G * s->npp_max <= PC::YB * (N + 1) ? 1 : 0;
   const dim3 grid(s->nplanes, B ? b.nrows : plane_groups(s, nb));
-  if (s->yz_half)
-    plane_inv_kernel<N, R, TIN, true, B><<<grid, PC::NT, plane_smem<false>(s), st>>>(
-        (const TIN*)pk, nb, s->npw_stride, (cplx<R>*)T, sphere_tab(s), (const cplx<R>*)tw, s->ncol_max, stage, b.jobs,
-        b.rows);
-  else
-    plane_inv_kernel<N, R, TIN, false, B><<<grid, PC::NT, plane_smem<false>(s), st>>>(
-        (const TIN*)pk, nb, s->npw_stride, (cplx<R>*)T, sphere_tab(s), (const cplx<R>*)tw, s->ncol_max, stage, b.jobs,
-        b.rows);
+  plane_inv_kernel<N, R, TIN, HB, B><<<grid, PC::NT, plane_smem<false>(s), st>>>(
+      (const TIN*)pk, nb, s->npw_stride, (cplx<R>*)T, sphere_tab(s), (const cplx<R>*)tw, s->ncol_max, stage, b.jobs,
+      b.rows);
+}
+
+template <int N, bool HB, bool B>
+static void plane_inv_h(const ks_system* s, int nb, const void* pk, bool in_fp64, void* T, const BatchRef& b,
+                        hipStream_t st) {
+  if (!mixed(s)) plane_inv_t<N, double, double2, HB, B>(s, nb, pk, T, s->d_tw1, b, st);
+  else if (in_fp64) plane_inv_t<N, float, double2, HB, B>(s, nb, pk, T, s->d_tw1f, b, st);
+  else plane_inv_t<N, float, float2, HB, B>(s, nb, pk, T, s->d_tw1f, b, st);
 }
 
 template <int N, bool B>
 static void plane_inv_n(const ks_system* s, int nb, const void* pk, bool in_fp64, void* T, const BatchRef& b,
                         hipStream_t st) {
-  if (!mixed(s)) plane_inv_t<N, double, double2, B>(s, nb, pk, T, s->d_tw1, b, st);
-  else if (in_fp64) plane_inv_t<N, float, double2, B>(s, nb, pk, T, s->d_tw1f, b, st);
-  else plane_inv_t<N, float, float2, B>(s, nb, pk, T, s->d_tw1f, b, st);
+  if (s->yz_half) plane_inv_h<N, true, B>(s, nb, pk, in_fp64, T, b, st);
+  else plane_inv_h<N, false, B>(s, nb, pk, in_fp64, T, b, st);
 }
 
 bool launch_plane_inv(const ks_system* s, int nb, const void* pk, bool in_fp64, void* T, hipStream_t st) {
@@ -87,28 +89,34 @@ bool launch_plane_inv_batch(const ks_system* s, const BatchJob* jobs, const int4
   }
 }
 
-template <int N, typename R, typename TW, bool B>
+template <int N, typename R, typename TW, bool HB, bool B>
 static void plane_fwd_t(const ks_system* s, int nb, const void* U, const void* win, void* wout, void* acc, void* acc2,
                         HMode mode, Taylor tay, int next, void* T, const void* tw, const BatchRef& b, hipStream_t st) {
-  using PC = pcfg<N, R, true>;
   const dim3 grid(s->nplanes, B ? b.nrows : plane_groups(s, nb));
-  auto* k = s->yz_half ? plane_fwd_kernel<N, R, TW, true, B> : plane_fwd_kernel<N, R, TW, false, B>;
-  k<<<grid, PC::NT, plane_smem<true>(s), st>>>((const cplx<R>*)U, nb, (const TW*)win, (cplx<R>*)wout, (double2*)acc,
-                                               (double2*)acc2, s->npw_stride, s->npw_stride, sphere_tab(s), s->d_kin,
-                                               (const cplx<R>*)tw, s->ncol_max, (int)mode, tay, next, (cplx<R>*)T,
-                                               b.jobs, b.rows);
+  plane_fwd_kernel<N, R, TW, HB, B><<<grid, pcfg<N, R, true, HB>::NT, plane_smem<true>(s), st>>>(
+      (const cplx<R>*)U, nb, (const TW*)win, (cplx<R>*)wout, (double2*)acc, (double2*)acc2, s->npw_stride, s->npw_stride,
+      sphere_tab(s), s->d_kin, (const cplx<R>*)tw, s->ncol_max, (int)mode, tay, next, (cplx<R>*)T, b.jobs,
+      b.rows);
+}
+
+template <int N, bool HB, bool B>
+static void plane_fwd_h(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
+                        void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, const BatchRef& b,
+                        hipStream_t st) {
+  if (!mixed(s))
+    plane_fwd_t<N, double, double2, HB, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1, b, st);
+  else if (win_fp64)
+    plane_fwd_t<N, float, double2, HB, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1f, b, st);
+  else
+    plane_fwd_t<N, float, float2, HB, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1f, b, st);
 }
 
 template <int N, bool B>
 static void plane_fwd_n(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,
                         void* acc, void* acc2, HMode mode, Taylor tay, int next, void* T, const BatchRef& b,
                         hipStream_t st) {
-  if (!mixed(s))
-    plane_fwd_t<N, double, double2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1, b, st);
-  else if (win_fp64)
-    plane_fwd_t<N, float, double2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1f, b, st);
-  else
-    plane_fwd_t<N, float, float2, B>(s, nb, U, win, wout, acc, acc2, mode, tay, next, T, s->d_tw1f, b, st);
+  if (s->yz_half) plane_fwd_h<N, true, B>(s, nb, U, win, win_fp64, wout, acc, acc2, mode, tay, next, T, b, st);
+  else plane_fwd_h<N, false, B>(s, nb, U, win, win_fp64, wout, acc, acc2, mode, tay, next, T, b, st);
 }
 
 bool launch_plane_fwd(const ks_system* s, int nb, const void* U, const void* win, bool win_fp64, void* wout,

@@ -9,11 +9,17 @@
 
 namespace ks {
 
+template <int N, typename R, bool HB>
+static void box_inv_h(const ks_system* s, int nb, const double2* box, void* T, const void* tw, hipStream_t st) {
+  plane_inv_kernel<N, R, double2, HB, false, true>
+      <<<dim3(s->nplanes, plane_groups(s, nb)), pcfg<N, R, false, HB>::NT, plane_smem<false>(s), st>>>(
+          box, nb, 0, (cplx<R>*)T, sphere_tab(s), (const cplx<R>*)tw, s->ncol_max, 0, nullptr, nullptr);
+}
+
 template <int N, typename R>
 static void box_inv_n(const ks_system* s, int nb, const double2* box, void* T, const void* tw, hipStream_t st) {
-  auto* k = s->yz_half ? plane_inv_kernel<N, R, double2, true, false, true> : plane_inv_kernel<N, R, double2, false, false, true>;
-  k<<<dim3(s->nplanes, plane_groups(s, nb)), pcfg<N, R, false>::NT, plane_smem<false>(s), st>>>(
-      box, nb, 0, (cplx<R>*)T, sphere_tab(s), (const cplx<R>*)tw, s->ncol_max, 0, nullptr, nullptr);
+  if (s->yz_half) box_inv_h<N, R, true>(s, nb, box, T, tw, st);
+  else box_inv_h<N, R, false>(s, nb, box, T, tw, st);
 }
 
 bool launch_plane_inv_box(const ks_system* s, int nb, const double2* box, void* T, hipStream_t st) {
@@ -30,13 +36,20 @@ bool launch_plane_inv_box(const ks_system* s, int nb, const double2* box, void* 
   }
 }
 
+template <int N, typename R, bool HB>
+static void box_fwd_h(const ks_system* s, int nb, const void* U, const double2* in, double2* out, const void* tw,
+                      hipStream_t st) {
+  plane_fwd_kernel<N, R, double2, HB, false, true>
+      <<<dim3(s->n[0], plane_groups(s, nb)), pcfg<N, R, true, HB>::NT, plane_smem<true>(s), st>>>(
+          (const cplx<R>*)U, nb, in, nullptr, out, nullptr, 0, 0, sphere_tab(s), s->d_kin, (const cplx<R>*)tw, s->ncol_max,
+          (int)H_OUT, Taylor{{0.0, 0.0}, 0, {0.0, 0.0}}, 0, nullptr, nullptr, nullptr);
+}
+
 template <int N, typename R>
 static void box_fwd_n(const ks_system* s, int nb, const void* U, const double2* in, double2* out, const void* tw,
                       hipStream_t st) {
-  auto* k = s->yz_half ? plane_fwd_kernel<N, R, double2, true, false, true> : plane_fwd_kernel<N, R, double2, false, false, true>;
-  k<<<dim3(s->n[0], plane_groups(s, nb)), pcfg<N, R, true>::NT, plane_smem<true>(s), st>>>(
-      (const cplx<R>*)U, nb, in, nullptr, out, nullptr, 0, 0, sphere_tab(s), s->d_kin, (const cplx<R>*)tw, s->ncol_max,
-      (int)H_OUT, Taylor{{0.0, 0.0}, 0, {0.0, 0.0}}, 0, nullptr, nullptr, nullptr);
+  if (s->yz_half) box_fwd_h<N, R, true>(s, nb, U, in, out, tw, st);
+  else box_fwd_h<N, R, false>(s, nb, U, in, out, tw, st);
 }
 
 bool launch_plane_fwd_box(const ks_system* s, int nb, const void* U, const double2* in, double2* out, hipStream_t st) {

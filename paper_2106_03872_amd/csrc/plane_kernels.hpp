@@ -87,8 +87,26 @@ KS_PLANE_CFG(120, true, false, 512, 24, 27, 1, 1)
 KS_PLANE_CFG(120, true, true, 320, 24, 27, 1, 1)
 KS_PLANE_CFG(120, false, false, 384, 24, 27, 1, 1)
 KS_PLANE_CFG(120, false, true, 512, 24, 24, 1, 4)
+KS_PLANE_CFG(128, true, false, 384, 16, 60, 1, 1)
+KS_PLANE_CFG(128, true, true, 384, 16, 60, 1, 1)
+KS_PLANE_CFG(128, false, false, 384, 16, 60, 1, 1)
+KS_PLANE_CFG(128, false, true, 512, 16, 32, 1, 1)
 #undef KS_PLANE_CFG
-template <int N, typename R, bool FWD> using pcfg = plane_cfg<N, sizeof(R) == 8, FWD>;
+// The rows are for spheres inside the band.  Past it (not HB) a plane has up to
+// 0.6 N columns at a spacing of 0.42 bohr; from 80 points on the z-batch takes
+// those in one, and 80 FP64 the y-batch of 48 of its former split: a step of
+// 160 orbitals there 10.4 -> 9.4 ms (80^3 FP64; 10.1 with the former split of 384
+// threads and 48 columns), 5.6 -> 5.4 (80^3 complex64), 8.3 -> 7.8 (40 x 120^2
+// complex64), 11.0 -> 10.3 ms (40 x 128^2 complex64).  Below, larger z-batches
+// cost registers and were slower (48^3 complex64 1.41 -> 1.58 ms).
+template <int N, bool F64, bool FWD, bool HB>
+struct plane_split : plane_cfg<N, F64, FWD> {
+  using row = plane_cfg<N, F64, FWD>;
+  static constexpr int wide = (6 * N / 10 + 3) / 4 * 4;
+  static constexpr int YB = !HB && F64 && N == 80 ? 48 : row::YB;
+  static constexpr int ZB = !HB && N >= 80 && wide > row::ZB ? wide : row::ZB;
+};
+template <int N, typename R, bool FWD, bool HB> using pcfg = plane_split<N, sizeof(R) == 8, FWD, HB>;
 
 // Packed coefficients of a plane that a thread holds in registers across an
 // orbital's transforms: a band-limited plane has at most about 0.165 N^2.
@@ -173,14 +191,14 @@ __device__ __forceinline__ void plane_synthesis(C* Z, C* Y, const C* tw, const i
 // BATCH: one launch over several systems of the grid; the block's system
 // (its input, T and orbital count) comes from jobs[rows[blockIdx.y].x].
 template <int N, typename R, typename TIN, bool HB, bool BATCH = false, bool BOX = false>
-__global__ __launch_bounds__((pcfg<N, R, false>::NT)) __attribute__((amdgpu_waves_per_eu(pcfg<N, R, false>::W))) void plane_inv_kernel(const TIN* __restrict__ pk, int nb, int pk_stride,
+__global__ __launch_bounds__((pcfg<N, R, false, HB>::NT)) __attribute__((amdgpu_waves_per_eu(pcfg<N, R, false, HB>::W))) void plane_inv_kernel(const TIN* __restrict__ pk, int nb, int pk_stride,
                                                                      cplx<R>* __restrict__ Tout, SphereTab tab,
                                                                      const cplx<R>* __restrict__ twN, int ncol_max,
                                                                      int stage,
                                                                      const BatchJob* __restrict__ jobs = nullptr,
                                                                      const int4* __restrict__ rows = nullptr) {
   using C = cplx<R>;
-  constexpr int NTH = pcfg<N, R, false>::NT, YB = pcfg<N, R, false>::YB, ZB = pcfg<N, R, false>::ZB, G = pcfg<N, R, false>::G;
+  constexpr int NTH = pcfg<N, R, false, HB>::NT, YB = pcfg<N, R, false, HB>::YB, ZB = pcfg<N, R, false, HB>::ZB, G = pcfg<N, R, false, HB>::G;
   constexpr int EP = plane_ep(N, NTH);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   C* tw = reinterpret_cast<C*>(smem_raw);
@@ -284,13 +302,13 @@ __global__ __launch_bounds__((pcfg<N, R, false>::NT)) __attribute__((amdgpu_wave
 // BATCH: as plane_inv_kernel; U, win, wout, acc, T and the orbital count come
 // from the block's job (no second accumulator).
 template <int N, typename R, typename TW, bool HB, bool BATCH = false, bool BOX = false>
-__global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves_per_eu(pcfg<N, R, true>::W))) void plane_fwd_kernel(
+__global__ __launch_bounds__((pcfg<N, R, true, HB>::NT)) __attribute__((amdgpu_waves_per_eu(pcfg<N, R, true, HB>::W))) void plane_fwd_kernel(
     const cplx<R>* __restrict__ Uin, int nb, const TW* win, cplx<R>* __restrict__ wout, double2* acc, double2* acc2,
     int pk_stride, int acc_stride, SphereTab tab, const double* __restrict__ kin, const cplx<R>* __restrict__ twN,
     int ncol_max, int mode, Taylor tay, int next, cplx<R>* __restrict__ Tout,
     const BatchJob* __restrict__ jobs = nullptr, const int4* __restrict__ rows = nullptr) {
   using C = cplx<R>;
-  constexpr int NTH = pcfg<N, R, true>::NT, YB = pcfg<N, R, true>::YB, ZB = pcfg<N, R, true>::ZB, G = pcfg<N, R, true>::G;
+  constexpr int NTH = pcfg<N, R, true, HB>::NT, YB = pcfg<N, R, true, HB>::YB, ZB = pcfg<N, R, true, HB>::ZB, G = pcfg<N, R, true, HB>::G;
   constexpr int EP = plane_ep(N, NTH);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   C* tw = reinterpret_cast<C*>(smem_raw);
@@ -488,12 +506,15 @@ __global__ __launch_bounds__((pcfg<N, R, true>::NT)) __attribute__((amdgpu_waves
 
 // ------------------------------------------------------------------ launchers
 
-// Plane size, precision and direction -> f(config)
+// Plane size, precision, direction and band -> f(config, plane size)
 template <bool FWD, class F>
 void with_plane_cfg(const ks_system* s, F&& f) {
   switch (s->n[1]) {
-#define KS_CASE(v) \
-  case v: mixed(s) ? f(plane_cfg<v, false, FWD>{}) : f(plane_cfg<v, true, FWD>{}); break;
+#define KS_CASE(v)                                                                                         \
+  case v:                                                                                                  \
+    if (mixed(s)) s->yz_half ? f(plane_split<v, false, FWD, true>{}) : f(plane_split<v, false, FWD, false>{}); \
+    else s->yz_half ? f(plane_split<v, true, FWD, true>{}) : f(plane_split<v, true, FWD, false>{});        \
+    break;
     KS_SIZES(KS_CASE)
 #undef KS_CASE
     default:
