@@ -153,8 +153,8 @@ bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4
 //   E_cut = 10 Ha from a spacing of 0.30 bohr on at 128 points, 0.36 at 120
 //   in complex64, 0.48 at 72 in FP64, 0.58 at 40 and 96 in complex64, 48 and
 //   60 in FP64, 64 and 80 in both.
-// - In FP64 at 60, 72 and 80 points the synthesis runs slower in the analysis's
-//   work split than in its own, by more than a launch once the launch has over
+// - In FP64 at 60, 72 and 80 points, in the band, the synthesis runs slower in the
+//   analysis's work split than in its own, by more than a launch once the launch has over
 //   about eight blocks per compute unit.  Steps of 4 H psi, two launches against
 //   one, default group caps, us: 60^3 / 64 orbitals (1792 blocks) 706 and 697, /
 //   96 (2688) 968 and 981, / 160 1531 and 1559; 72^3 / 48 (1584) 877 and 865, /
@@ -167,7 +167,7 @@ bool launch_plane_fwd_batch(const ks_system* s, const BatchJob* jobs, const int4
 // 22589 and 22098 / 512): no line between sizes or launches separates those.
 bool plane_next(const ks_system* s, long long orbitals) {
   const int n = s->n[1];
-  if (!mixed(s) && (n == 60 || n == 72 || n == 80) && s->nplanes * orbitals > 2048) return false;
+  if (!mixed(s) && s->yz_half && (n == 60 || n == 72 || n == 80) && s->nplanes * orbitals > 2048) return false;
   bool fits = false;
   with_plane_cfg<true>(s, [&](auto c) {
     fits = (size_t)decltype(c)::G * s->npp_max <= (size_t)decltype(c)::YB * (n + 1);
