@@ -21,12 +21,19 @@ size_t plane_lds_bytes(const ks_system* s) {
 
 // Orbitals per plane block for a launch over `total` orbitals: up to pg_max,
 // fewer when the launch would have fewer than about 4 blocks per CU, but the
-// G orbitals that a block transforms together.
+// G orbitals that a block transforms together, unless one orbital per block
+// leaves compute units idle: up to 256 blocks, 768 in complex64 from 32 points
+// on and 1024 of a wave each at 8 and 12 points.  A step of 4 H psi with and
+// without that, us: 12 x 8 x 8 / 16 FP64 75 -> 70, / 160 78 -> 74; 20^3 / 16 77 ->
+// 75 (/ 32, 288 blocks, 79 -> 81: not); 32^3 / 16 complex64 86 -> 75, / 48 103 -> 94;
+// 40^3 / 8 complex64 104 -> 92, / 32 149 -> 140 (/ 64, 1088 blocks, 211 -> 224: not).
 int plane_group_size(const ks_system* s, long long total) {
   int G = 1;
   with_plane_cfg<false>(s, [&](auto c) { G = decltype(c)::G; });
   with_plane_cfg<true>(s, [&](auto c) { G = std::max(G, decltype(c)::G); });
   G = std::min(G, s->pg_max);
+  const int one = s->n[1] <= 12 ? 1024 : mixed(s) && s->n[1] >= 32 ? 768 : 256;
+  if (s->nplanes * total <= one) return 1;
   long long g = (long long)s->nplanes * total / (256 * 4);
   g = g < G ? G : (g > s->pg_max ? s->pg_max : g);
   return (int)(g / G * G);
