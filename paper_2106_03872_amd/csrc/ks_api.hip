@@ -2357,11 +2357,13 @@ ks_status ks_propagate_batch(ks_state* const* states, int nstates, double dt, in
 // a lane has KB_CACHED_POINTS).  Where lanes are too few or groups at their
 // limit, the layout grows with the points: measured on the host for random
 // spheres of one radius and of radii 3.5 to 9 grid spacings, up to the densest
-// that a tile takes, it then has at most 1.97 entries per point and projector.  As
-// for the partials, a slot is taken to have at least eight points.
+// that a tile takes, it then has at most 1.97 entries per point and projector.
+// Slots are taken to have at least FOOTPRINT_SLOT_POINTS points (spheres of a
+// radius of 3.2 grid spacings have; of 6.4, 50 to 70).
+constexpr double FOOTPRINT_SLOT_POINTS = 16.0;
 static double proj_table_bytes(const int n[3], double npoints, double np) {
   if (npoints <= 0.0) return 0.0;
-  const double slots = npoints / 8.0;
+  const double slots = npoints / FOOTPRINT_SLOT_POINTS;
   double most = 0.0;
   for (int shape = 0; shape < 4; ++shape) {
     if (!x_shape_available(n[0], shape)) continue;
@@ -2400,7 +2402,7 @@ ks_status ks_plan_footprint(const int n[3], const double L[3], double ecut, int 
                                                         // work box of the Hartree solve; reductions
   b += (double)((cb + 7) / 8) * N * 8.0;                // partial densities
   b += proj_table_bytes(n, npoints, np) + 64.0 * 1024;  // projection tables; small tables and alignment
-  b += (double)cb * npoints * np * 16.0 / 8.0;          // projection partials (upper bound)
+  b += (double)cb * npoints / FOOTPRINT_SLOT_POINTS * np * 16.0;   // projection partials (upper bound)
   b += (double)norb * stride * 16.0;                    // resident state
   b += 2.0 * norb * norb * 16.0 + (double)gemm_part_bytes(norb, h.npw);   // orthonormalisation
   *bytes = (unsigned long long)b;

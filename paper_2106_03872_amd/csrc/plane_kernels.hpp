@@ -11,22 +11,32 @@ namespace ks {
 // threads per block, columns per y-batch, columns per z-batch, orbitals
 // transformed together.  A compute unit needs about three waves per SIMD here
 // (a lone wave issues a vector instruction only every other slot), and every
-// batch stage ends at a block barrier, so the rows are the fastest of eight
-// measured splits per size, precision and direction, under these rules:
+// batch stage ends at a block barrier.  At 24 to 120 points the rows are the
+// fastest of eight measured splits per size, precision and direction (spheres in
+// the band, the analysis without the chained synthesis); at 8 to 20 points they
+// follow the first rule, unswept; at 128 points the complex64 analysis is the
+// fastest of eleven.  The rules:
 //  - small planes take several orbitals at once (or a smaller block): a plane
-//    of 16 to 48 points leaves most lanes of a 64-column batch without work;
+//    of 8 to 40 points leaves most lanes of a 64-column batch without work;
 //  - the z-batch follows the sphere's column count (about 0.45 N), not the
 //    y-batch;
-//  - from 60 points on in FP64 the y-batch shrinks until two blocks fit a
-//    compute unit; a synthesis batch stores whole 64-byte runs of T (rows of
-//    30 complex64 took twice as long as rows of 60 or 20).
+//  - in FP64 at 60, 64 and 72 points and for the synthesis at 80 the y-batch
+//    shrinks until two blocks fit a compute unit (47 to 75 KB each); the analysis
+//    at 80 and both passes from 96 on keep a larger one and one block (97 to 150 KB);
+//  - a synthesis batch of complex64 stores rows of whole 32-byte sectors of T:
+//    rows of 30 (240 bytes) took twice as long as rows of 60 or 20.
 // Per launch, one block of 384 threads and 64 or 48 columns for all sizes
-// against these rows: 64^2 FP64 / 128 orbitals synthesis 82 and 56 us, analysis
-// 93 and 70 us; 32^2 complex64, 262 orbitals in a batch: 19 and 10, 33 and 13
-// us; 40^2 FP64 / 33: 13.3 and 9.4, 16.9 and 9.9 us; 96^2 complex64 / 512: 398
-// and 376, 531 and 472 us; 120^2 complex64 / 1024: 1783 and 1717, 2752 and 2404
-// us (T or U streams at 3.6 and 2.9 TB/s there; 96^2 FP64 at 5.0 and 5.0, near
-// the rate of a large copy, which bounds it).
+// against these rows, us: 8^2 FP64 / 512 orbitals (12 planes of n0) synthesis 9.8
+// and 6.6, analysis 13.6 and 8.2; 16^2 FP64 / 512 16.3 and 10.7, 23.8 and 11.7; 20^2
+// FP64 / 512 22.6 and 13.9, 34.7 and 23.7; 64^2 FP64 / 128 82 and 56, 93 and 70;
+// 32^2 complex64, 262 orbitals in a batch 19 and 10, 33 and 13; 40^2 FP64 / 33 13.3
+// and 9.4, 16.9 and 9.9; 96^2 complex64 / 512 398 and 376, 531 and 472; 120^2
+// complex64 / 1024 1783 and 1717, 2752 and 2404; 128^2 complex64 / 160 (40 planes of
+// n0) 120 and 110, 169 and 151, FP64 / 160 258 and 229, 350 and 352 (T or U streams
+// at 3.6 and 2.9 TB/s at 120^2; 96^2 FP64 at 5.0 and 5.0, near the rate of a large
+// copy, which bounds it).
+// The four waves per SIMD asked for at 96 and 120 points in complex64 spill one to
+// five registers of the analysis from FP64 orbitals (one of a step's four).
 template <int N, bool F64, bool FWD> struct plane_cfg { static constexpr int NT = 384, YB = 16, ZB = 16, G = 1, W = 1; };
 // (points, FP64, analysis) -> threads, y-batch, z-batch, orbitals, waves per SIMD to fit the registers to
 #define KS_PLANE_CFG(n, f64, fwd, nt, yb, zb, g, w) \
